@@ -158,6 +158,18 @@ __device__ __forceinline__ uint32_t hash_index(int x, int y, int z, uint32_t mas
     return hash_raw(x, y, z) & mask;
 }
 
+// the excess chain of bucket b: the key's entry id, or -1
+__device__ __forceinline__ int32_t walk_chain(const HashView &h, uint32_t b, unsigned long long key)
+{
+    int32_t x_i = h.head[b];
+    while (x_i >= 0) {
+        const Excess E = h.excess[x_i];
+        if (E.key == key) return 2 * h.n_buckets + x_i;
+        x_i = E.next;
+    }
+    return -1;
+}
+
 // the bucket's two entries, then (both taken) the excess chain; returns the
 // entry id, which is also the block's place in the voxel block array, or -1
 __device__ __forceinline__ int32_t probe_bucket(const HashView &h, uint32_t b, unsigned long long key)
@@ -166,13 +178,7 @@ __device__ __forceinline__ int32_t probe_bucket(const HashView &h, uint32_t b, u
     if (keys.x == key) return 2 * (int32_t)b;
     if (keys.y == key) return 2 * (int32_t)b + 1;
     if (keys.y == 0ull) return -1;   // a free slot: the bucket has no chain
-    int32_t x_i = h.head[b];
-    while (x_i >= 0) {
-        const Excess E = h.excess[x_i];
-        if (E.key == key) return 2 * h.n_buckets + x_i;
-        x_i = E.next;
-    }
-    return -1;
+    return walk_chain(h, b, key);
 }
 
 // Read-only retrieval (section "Hash Table Operations"): the bucket's two
