@@ -156,13 +156,19 @@ template <int FMT, bool REF>
 __device__ __forceinline__ float cube_F(const Cube<FMT> &cb, const VoxSrc<FMT, REF> &src, int vx, int vy, int vz)
 {
     const int32_t ptr = cube_block(cb, vx, vy, vz);
-    if (ptr < 0) return 1.0f;
+    // The 16-bit forms read block 0 for an absent block and drop the value: their
+    // loads fill half a register, and under a branch each was waited for (frame of
+    // 1280x720 at 4 mm: 222 -> 213 us).  The float form is faster with the branch
+    // (77.4 against 80.2 us at 640x480): its absent lanes then make no request.
+    if (FMT == ITM_VOX_F32 && ptr < 0) return 1.0f;
     bool r = false;
     if (REF) {
         const int c = ((vx >> 3) != cb.bx0 ? 1 : 0) | ((vy >> 3) != cb.by0 ? 2 : 0) | ((vz >> 3) != cb.bz0 ? 4 : 0);
         r = (cb.rmask >> c) & 1u;
     }
-    return src.read(ptr, r, (int32_t)((vx & 7) | (vy & 7) << 3 | (vz & 7) << 6));
+    const float F = src.read(FMT == ITM_VOX_F32 ? ptr : max(ptr, 0), r,
+                             (int32_t)((vx & 7) | (vy & 7) << 3 | (vz & 7) << 6));
+    return ptr < 0 ? 1.0f : F;
 }
 
 // the 8 lattice voxels of the cell with corner i
