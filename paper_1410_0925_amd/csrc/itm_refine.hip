@@ -4,14 +4,25 @@
 // block with a one-voxel halo, or the 8^3 block zero-padded) to the 8^3 block,
 // 16 input and 16 output channels (layer 1 uses 2 real input channels, layer 4
 // one real output channel; the others hold zeros).  As an implicit GEMM per
-// block: M = 512 voxels, N = 16 output channels, K = 27 taps x 16 channels, two
+// block: M = 16 output channels, N = 512 voxels, K = 27 taps x 16 channels, two
 // taps per K step of gfx950's v_mfma_f32_16x16x32_bf16 (layer 1, with its 2 real
-// input channels stored as 4, takes 8 taps per K step).  A workgroup of 16 waves
-// takes a block; wave w owns the voxel tiles 2w, 2w + 1 of its 32 (16-voxel
-// tiles), so each SIMD has 4 waves to overlap LDS reads and MFMA chains (the
-// LDS footprint allows few workgroups per CU).  Activations live in LDS
-// as bf16 [voxel][channel], so a lane's 8 K values are one 16-byte LDS read;
-// weights are read from global memory (L1-resident) as bf16.
+// input channels stored as 4, takes 8 taps per K step).
+//
+// What bounds it is LDS: a K step of 16 voxels is a 1 KB fragment, 8 cycles of the
+// CU's 128 bytes a cycle, for 16 cycles of one of its four matrix cores.  So
+//   * activations lie in LDS with their halo of zeros, [8-channel half][10^3][8]:
+//     a fragment is one conflict-free 16-byte read per lane at a constant offset
+//     from one of three lane addresses, with no bounds test;
+//   * a wave takes a column of planes of one pair of y rows, marching in z: the
+//     fragments of a plane serve the taps below and above it (82 reads for the
+//     112 K steps of 8 planes);
+//   * a layer's weights are loaded once per wave into 56 registers;
+//   * the voxels are MFMA columns, so a lane ends with 4 consecutive channels of
+//     one voxel and stores them in one write.
+// Inference runs a layer in place in one 33 KB buffer, 4 waves of 8 planes per
+// workgroup, 3 workgroups per CU.  Measured (a forward pass of 4001 blocks): 214 us
+// when every wave read each tap's voxels, under a bounds test, and its weights for
+// 2 tiles of 16 voxels; 90 us (688 TFLOP/s) so, of which 60 are the LDS reads.
 //
 // Back-propagation reuses the same operation: the data gradient is the
 // convolution of the output gradient with the tap-flipped, channel-transposed
@@ -25,8 +36,8 @@
 
 namespace itm {
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -42,11 +53,6 @@ __device__ __forceinline__ uint16_t to_bf16(float f)
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-__device__ __forceinline__ f32x4 mfma16(bf16x4 a, bf16x4 b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-
 // 16 x 16 x 32: a lane holds 8 consecutive K values of its row (A) / column (B)
 __device__ __forceinline__ f32x4 mfma32(i32x4 a, i32x4 b, f32x4 c)
 {
@@ -54,165 +60,231 @@ __device__ __forceinline__ f32x4 mfma32(i32x4 a, i32x4 b, f32x4 c)
                                                    0, 0, 0);
 }
 
-// LDS working set of one block (16-byte aligned rows: a lane's 8 channels are one
-// read).  Training keeps all three hidden activations for the backward pass
-// (92 KB, with the weight gradient's transposed copies 125 KB: one workgroup per
-// CU); inference alternates two (42 KB: two 16-wave workgroups per CU).
-template <int NACT>
-struct alignas(16) RefineAct {
-    uint16_t x0[1000 * 4];          // network input, 10^3 grid, channels F, W/max_w, 0, 0
-    uint16_t act[NACT][512 * kC];   // layer l's output (8^3 x 16) in act[l % NACT]
-    float centre[512];              // F of the block itself (float32), for the residual
-};
-struct alignas(16) RefineLds : RefineAct<3> {
-    uint16_t grad[2][512 * kC];     // back-propagated gradient, ping-pong
-};
-using RefineLdsInf = RefineAct<2>;
+// A block's 16-channel grid in LDS, its halo of zeros included: channels 8 h .. 8 h
+// + 7 of voxel (x, y, z) at kHalf h + 8 (x + 1 + 10 (y + 1) + 100 (z + 1)).  The pad
+// takes the reads of a plane past the last (their lanes' values are dropped).
+constexpr int kPlane = 100 * 8, kHalf = 10 * kPlane;
+constexpr int kGrid = 2 * kHalf + kPlane;
 
-// one wave's TPW tiles of a 3^3 convolution: acc[t] (lane: voxel 4 kq + r of tile
-// TPW w + t, channel lane & 15) = sum over taps of A(tap) x W(tap).
-// K order of one instruction (lane group kq = lane >> 4 holds K 8 kq .. 8 kq + 7):
-//   layer 0 (4 stored input channels): taps 8 g + 2 kq and 8 g + 2 kq + 1, their
-//            channels 0..3 each, g = 0..3 (taps past 26 read zeros);
-//   layers 1..3 and data gradients (16 channels): tap 2 p + (kq >> 1), channels
-//            8 (kq & 1) .. + 7, p = 0..13.
-template <int TPW>
-__device__ __forceinline__ void conv_tiles(const uint16_t *x0, const uint16_t *in, int layer,
-                                           const uint16_t *Wl, bool flip, int wave, int lane,
-                                           f32x4 acc[TPW])
+// K steps 0 .. 13 of a layer with 16 input channels, as a lane holds them: K step p
+// is taps 2 p (lanes 0-31) and 2 p + 1 (lanes 32-63), channels 8 h .. 8 h + 7 with h =
+// (lane >> 4) & 1; tap 27 is zero.  W: bf16 [tap][row][channel].
+__device__ __forceinline__ void load_weights(const uint16_t *W, bool flip, int lane, i32x4 (&w)[14])
 {
-    const int kq = lane >> 4, n = lane & 15;
+    const int n = lane & 15, h = (lane >> 4) & 1, s = lane >> 5;
+    int at = (flip ? (kTaps - 1) * kC * kC : 0) + n * kC + 8 * h;
+    // opaque: the 14 addresses would otherwise be kept over the whole kernel
+    asm volatile("" : "+v"(at));
+    const int step = flip ? -kC * kC : kC * kC;
+#pragma unroll
+    for (int p = 0; p < 14; p++)
+        w[p] = *reinterpret_cast<const i32x4 *>(&W[at + (p < 13 ? 2 * p + s : 26) * step]);
+    if (s) w[13] = i32x4{0, 0, 0, 0};
+}
+
+// acc[j] (lane: voxel column lane & 15, channels 4 (lane >> 4) + r) = the
+// convolution at the 16 voxels of rows 2 yp, 2 yp + 1 of plane z0 + j: for every
+// output plane the K steps in order, taps 0 .. 26 in pairs.  Planes are visited
+// once, r = 0 .. NZ + 1 (input plane z0 - 1 + r), tap = 9 dz + in-plane tap:
+//   E  in-plane pairs (0,1) (2,3) (4,5) (6,7): taps of dz = 0 for plane r, of dz = 2
+//      for plane r - 2;
+//   S  in-plane tap 8 of the plane before with tap 0 of this one: taps 8, 9 of
+//      plane r - 1; its first half, alone, is tap 26 of plane r - 3;
+//   O  in-plane pairs (1,2) (3,4) (5,6) (7,8): dz = 1 of plane r - 1.
+template <int NZ>
+__device__ __forceinline__ void conv16(const uint16_t *grid, const i32x4 (&w)[14], int yp, int z0, int lane,
+                                       f32x4 (&acc)[NZ])
+{
+    const int n = lane & 15, h = (lane >> 4) & 1, s = lane >> 5;
+    // in-plane tap 0 of input plane r = 0; the second half of the lanes reads the
+    // pair's other tap, 1, 8 or (the next plane) 78 voxels on
+    const uint16_t *base = grid + h * kHalf + (z0 * 100 + (2 * yp + (n >> 3)) * 10 + (n & 7)) * 8;
+    const uint16_t *b1 = base + s * 8, *b8 = base + s * 64, *b78 = base + s * 624;
     const i32x4 zero = {0, 0, 0, 0};
 #pragma unroll
-    for (int t = 0; t < TPW; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (layer == 0) {
-#pragma unroll 1
-        for (int g = 0; g < 4; g++) {
-            const int ta = 8 * g + 2 * kq, tb = ta + 1;
-            const bool va = ta < kTaps, vb = tb < kTaps;
-            const uint2 wa = va ? *reinterpret_cast<const uint2 *>(&Wl[(ta * kC + n) * kC]) : make_uint2(0, 0);
-            const uint2 wb = vb ? *reinterpret_cast<const uint2 *>(&Wl[(tb * kC + n) * kC]) : make_uint2(0, 0);
-            const i32x4 b = {(int)wa.x, (int)wa.y, (int)wb.x, (int)wb.y};
-            const int oa = (ta % 3) + 10 * ((ta / 3) % 3) + 100 * (ta / 9);
-            const int ob = (tb % 3) + 10 * ((tb / 3) % 3) + 100 * (tb / 9);
+    for (int j = 0; j < NZ; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    i32x4 S = zero;
 #pragma unroll
-            for (int t = 0; t < TPW; t++) {
-                const int vox = (wave * TPW + t) * 16 + n;
-                const int u = (vox & 7) + 10 * ((vox >> 3) & 7) + 100 * (vox >> 6);
-                const uint2 xa = va ? *reinterpret_cast<const uint2 *>(&x0[(u + oa) * 4]) : make_uint2(0, 0);
-                const uint2 xb = vb ? *reinterpret_cast<const uint2 *>(&x0[(u + ob) * 4]) : make_uint2(0, 0);
-                const i32x4 a = {(int)xa.x, (int)xa.y, (int)xb.x, (int)xb.y};
-                acc[t] = mfma32(a, b, acc[t]);
-            }
-        }
-        return;
-    }
-    const int h = kq & 1;
-#pragma unroll 1
-    for (int p = 0; p < (kTaps + 1) / 2; p++) {
-        const int tap = 2 * p + (kq >> 1);
-        const bool valid = tap < kTaps;
-        const int wt = flip ? kTaps - 1 - tap : tap;
-        // B operand: 8 consecutive reduction channels of output column n
-        const i32x4 b = valid ? *reinterpret_cast<const i32x4 *>(&Wl[(wt * kC + n) * kC + 8 * h]) : zero;
-        const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
+    for (int r = 0; r < NZ + 2; r++) {
+        const bool edge = NZ == 8 && (r == 0 || r == NZ + 1);   // the halo plane: zeros
+        auto at = [&](const uint16_t *b, int a) -> i32x4 {      // the pair from in-plane tap a of plane r
+            return *reinterpret_cast<const i32x4 *>(b + (r * 100 + a % 3 + 10 * (a / 3)) * 8);
+        };
+        if (r >= 1 && r <= NZ) {
+            acc[r - 1] = mfma32(w[4], S, acc[r - 1]);
 #pragma unroll
-        for (int t = 0; t < TPW; t++) {
-            const int vox = (wave * TPW + t) * 16 + n;
-            const int ux = (vox & 7) + dx - 1, uy = ((vox >> 3) & 7) + dy - 1, uz = (vox >> 6) + dz - 1;
-            const bool inside = valid && (unsigned)ux < 8u && (unsigned)uy < 8u && (unsigned)uz < 8u;
-            const i32x4 a = inside ? *reinterpret_cast<const i32x4 *>(&in[(ux + 8 * uy + 64 * uz) * kC + 8 * h])
-                                   : zero;
-            acc[t] = mfma32(a, b, acc[t]);
+            for (int q = 0; q < 4; q++) acc[r - 1] = mfma32(w[5 + q], at(q == 2 ? b8 : b1, 2 * q + 1), acc[r - 1]);
         }
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const i32x4 E = edge ? zero : at(q == 1 ? b8 : b1, 2 * q);
+            if (r < NZ) acc[r] = mfma32(w[q], E, acc[r]);
+            if (r >= 2) acc[r - 2] = mfma32(w[9 + q], E, acc[r - 2]);
+        }
+        S = at(b78, 8);
+        if (r >= 2) acc[r - 2] = mfma32(w[13], s ? zero : S, acc[r - 2]);
     }
 }
 
-// forward through the 4 layers; leaves activations in L.act and returns, for the
-// lanes with output channel 0, the residual delta of their 4 voxels per tile
-template <int NACT, int TPW>
-__device__ void refine_forward(RefineAct<NACT> &L, const RefineParams &P, int wave, int lane, f32x4 delta[TPW])
+// Layer 1: K step g holds taps 8 g + 2 kq and 8 g + 2 kq + 1, 4 stored channels each
+// (lane group kq = lane >> 4); taps past 26 are zero.
+__device__ __forceinline__ void load_weights0(const uint16_t *W, int lane, i32x4 (&w)[4])
 {
     const int kq = lane >> 4, n = lane & 15;
-    f32x4 acc[TPW];
-    for (int l = 0; l < kLayers; l++) {
-        const uint16_t *in = l == 0 ? nullptr : L.act[(l - 1) % NACT];
-        conv_tiles<TPW>(L.x0, in, l, P.Wf + (size_t)l * kTaps * kC * kC, false, wave, lane, acc);
-        const float b = P.bias[l * kC + n];
-        if (l < kLayers - 1) {
 #pragma unroll
-            for (int t = 0; t < TPW; t++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int vox = (wave * TPW + t) * 16 + 4 * kq + r;
-                    L.act[l % NACT][vox * kC + n] = to_bf16(fmaxf(acc[t][r] + b, 0.0f));
-                }
-        } else {
-#pragma unroll
-            for (int t = 0; t < TPW; t++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) delta[t][r] = acc[t][r] + b;
-        }
-        __syncthreads();
+    for (int g = 0; g < 4; g++) {
+        const int ta = 8 * g + 2 * kq, tb = ta + 1;
+        uint2 wa = *reinterpret_cast<const uint2 *>(&W[(min(ta, kTaps - 1) * kC + n) * kC]);
+        uint2 wb = *reinterpret_cast<const uint2 *>(&W[(min(tb, kTaps - 1) * kC + n) * kC]);
+        if (ta >= kTaps) wa = make_uint2(0, 0);
+        if (tb >= kTaps) wb = make_uint2(0, 0);
+        w[g] = i32x4{(int)wa.x, (int)wa.y, (int)wb.x, (int)wb.y};
     }
 }
 
-// fill L.x0 / L.centre from a float32 input block [2][10^3] in global memory
-template <int NACT>
-__device__ void load_input(RefineAct<NACT> &L, const float *in)
+template <int NZ>
+__device__ __forceinline__ void conv0(const uint16_t *x0, const i32x4 (&w)[4], int yp, int z0, int lane,
+                                      f32x4 (&acc)[NZ])
 {
-    for (int u = threadIdx.x; u < 1000; u += blockDim.x) {
-        const float F = in[u], W = in[1000 + u];
-        uint16_t *d = &L.x0[u * 4];
-        d[0] = to_bf16(F);
-        d[1] = to_bf16(W);
-        d[2] = 0;
-        d[3] = 0;
-        const int x = u % 10, y = (u / 10) % 10, z = u / 100;
-        if (x >= 1 && x <= 8 && y >= 1 && y <= 8 && z >= 1 && z <= 8)
-            L.centre[(x - 1) + 8 * (y - 1) + 64 * (z - 1)] = F;
+    const int kq = lane >> 4, n = lane & 15;
+    const uint16_t *base = x0 + (z0 * 100 + (2 * yp + (n >> 3)) * 10 + (n & 7)) * 4;
+#pragma unroll
+    for (int j = 0; j < NZ; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+        const int ta = 8 * g + 2 * kq, tb = ta + 1;
+        const int ca = min(ta, kTaps - 1), cb = min(tb, kTaps - 1);
+        const uint16_t *pa = base + (ca % 3 + 10 * (ca / 3 % 3) + 100 * (ca / 9)) * 4;
+        const uint16_t *pb = base + (cb % 3 + 10 * (cb / 3 % 3) + 100 * (cb / 9)) * 4;
+#pragma unroll
+        for (int j = 0; j < NZ; j++) {
+            uint2 xa = *reinterpret_cast<const uint2 *>(pa + j * 400);
+            uint2 xb = *reinterpret_cast<const uint2 *>(pb + j * 400);
+            if (g == 3) {   // taps 27 and on
+                if (ta >= kTaps) xa = make_uint2(0, 0);
+                if (tb >= kTaps) xb = make_uint2(0, 0);
+            }
+            acc[j] = mfma32(w[g], i32x4{(int)xa.x, (int)xa.y, (int)xb.x, (int)xb.y}, acc[j]);
+        }
     }
 }
 
-// The inference kernels' workgroups: kInferWaves waves, kInferTPW voxel tiles each
-constexpr int kInferWaves = 16;
-constexpr int kInferTPW = 32 / kInferWaves;
+// 4 channels of a lane's voxel, rounded to bf16
+__device__ __forceinline__ uint2 pack4(f32x4 v) { return __builtin_bit_cast(uint2, __builtin_convertvector(v, bf16x4)); }
+
+// where a lane's 4 channels of plane z0 lie in the grid (a plane on: + kPlane)
+__device__ __forceinline__ int grid_out(int yp, int z0, int lane)
+{
+    const int n = lane & 15, kq = lane >> 4;
+    return (kq >> 1) * kHalf + ((z0 + 1) * 100 + (2 * yp + (n >> 3) + 1) * 10 + (n & 7) + 1) * 8 + (kq & 1) * 4;
+}
+
+__device__ __forceinline__ f32x4 load_bias(const RefineParams &P, int l, int lane)
+{
+    return *reinterpret_cast<const f32x4 *>(&P.bias[l * kC + 4 * (lane >> 4)]);
+}
+
+__device__ __forceinline__ f32x4 relu(f32x4 v, f32x4 b)
+{
+    f32x4 o;
+#pragma unroll
+    for (int r = 0; r < 4; r++) o[r] = fmaxf(v[r] + b[r], 0.0f);
+    return o;
+}
+
+// The inference kernels' workgroups: 4 waves, wave w the rows 2 w, 2 w + 1 of all
+// 8 planes
+constexpr int kInferThreads = 256;
+struct alignas(16) InferLds {
+    uint16_t grid[kGrid];
+    uint16_t x0[1000 * 4];          // network input, 10^3 grid, channels F, W/max_w, 0, 0
+};
+
+// the grid's halo (and all else) zero: once per workgroup, the layers write the inside
+__device__ __forceinline__ void clear_grid(uint16_t *grid)
+{
+    for (int i = threadIdx.x; i < kGrid / 8; i += blockDim.x)
+        reinterpret_cast<i32x4 *>(grid)[i] = i32x4{0, 0, 0, 0};
+}
+
+__device__ __forceinline__ void store_x0(uint16_t *x0, int u, float F, float W)
+{
+    *reinterpret_cast<uint2 *>(&x0[u * 4]) = make_uint2((uint32_t)to_bf16(F) | (uint32_t)to_bf16(W) << 16, 0u);
+}
+
+// The 4 layers on L.x0 (every thread has stored its part).  delta[j]: the
+// residual of voxel column lane & 15 of plane j, on lanes 0-15.
+__device__ __forceinline__ void infer_layers(InferLds &L, const RefineParams &P, int wave, int lane, float (&delta)[8])
+{
+    f32x4 acc[8];
+    i32x4 w[14];
+    const int out = grid_out(wave, 0, lane);
+    {
+        i32x4 w0[4];
+        load_weights0(P.Wf, lane, w0);
+        __syncthreads();
+        conv0<8>(L.x0, w0, wave, 0, lane, acc);
+    }
+#pragma unroll 1
+    for (int l = 0; l < kLayers - 1; l++) {
+        const f32x4 b = load_bias(P, l, lane);
+        load_weights(P.Wf + (size_t)(l + 1) * kTaps * kC * kC, false, lane, w);
+        if (l > 0) __syncthreads();   // every wave has read the layer's input
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            *reinterpret_cast<uint2 *>(&L.grid[out + j * kPlane]) = pack4(relu(acc[j], b));
+        __syncthreads();
+        conv16<8>(L.grid, w, wave, 0, lane, acc);
+    }
+    const float b = P.bias[3 * kC];
+#pragma unroll
+    for (int j = 0; j < 8; j++) delta[j] = acc[j][0] + b;
+}
 
 // inference only: the refined F of each block
-__global__ __launch_bounds__(kInferWaves * 64) void k_refine_infer(RefineArgs a)
+__global__ __launch_bounds__(kInferThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_refine_infer(RefineArgs a)
 {
-    constexpr int TPW = kInferTPW;
-    __shared__ RefineLdsInf L;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int kq = lane >> 4, n = lane & 15;
+    __shared__ InferLds L;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    clear_grid(L.grid);
     for (int64_t blk = blockIdx.x; blk < a.n; blk += gridDim.x) {
-        load_input(L, a.in + blk * 2000);
-        __syncthreads();
-        f32x4 delta[TPW];
-        refine_forward<2, TPW>(L, a.P, wave, lane, delta);
-        if (n == 0) {
+        const float *in = a.in + blk * 2000;
+        for (int u = threadIdx.x; u < 1000; u += kInferThreads) store_x0(L.x0, u, in[u], in[1000 + u]);
+        float delta[8];
+        infer_layers(L, a.P, wave, lane, delta);
+        if (lane < 16) {
+            const int x = lane & 7, y = 2 * wave + (lane >> 3);
 #pragma unroll
-            for (int t = 0; t < TPW; t++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int vox = (wave * TPW + t) * 16 + 4 * kq + r;
-                    a.out[blk * 512 + vox] = fminf(fmaxf(L.centre[vox] + delta[t][r], -1.0f), 1.0f);
-                }
+            for (int j = 0; j < 8; j++) {
+                const float z = in[(x + 1) + 10 * (y + 1) + 100 * (j + 1)] + delta[j];
+                a.out[blk * 512 + x + 8 * y + 64 * j] = fminf(fmaxf(z, -1.0f), 1.0f);
+            }
         }
-        __syncthreads();
+        __syncthreads();   // the next block's layer 1 overwrites the grid
     }
 }
 
-// The training kernel's LDS (all activations and the gradients) allows one
-// workgroup per CU, so a block is split over 16 waves (4 per SIMD, 2 voxel tiles
-// and about 2 weight-gradient taps each) to hide its LDS and MFMA latencies.
-constexpr int kTrainWaves = 16;
-constexpr int kTrainTPW = 32 / kTrainWaves;
-
-// [channel][voxel] copies of a layer's output gradient and input for its weight
-// gradient (rows padded by 8 elements, so the 16-byte reads of lanes with
-// consecutive channels fall in different LDS banks)
+// Training: 8 waves, wave w rows 2 (w & 3), + 1 of planes 4 (w >> 2) .. + 3.  The
+// hidden activations are kept for the weight gradients as x-rows per channel,
+// [channel][z + 1][y + 1][x] with a halo of zero rows, the output gradient as
+// [channel][voxel] (both padded by 8 elements per channel, so the 16-byte reads of
+// lanes with consecutive channels fall in different LDS banks), beside the grid the
+// convolutions read, which holds the back-propagated gradient afterwards (142 KB:
+// one workgroup per CU).  A batch of 256 blocks is one block per CU, so the time is
+// one block's chain of layers: 44 us, 14 of them the weight gradients and 20 the six
+// convolutions at their LDS rate (68 us with 16 waves of 2 tiles, activations
+// copied to channel rows layer by layer).
+constexpr int kTrainWaves = 8, kTrainNZ = 4;
 constexpr int kRowT = 512 + 8;
+constexpr int kRowA = 100 * 8 + 8;
+struct alignas(16) TrainLds {
+    uint16_t grid[kGrid];
+    uint16_t x0[1000 * 4];
+    uint16_t x0T[2 * 100 * 16];       // the input's two real channels, [channel][z][y][x, padded to 16]
+    uint16_t aT[3][kC * kRowA];       // hidden activations
+    uint16_t gT[kC * kRowT];          // the current layer's output gradient
+    float red[2][kTrainWaves];
+};
 
 // 8 bf16 of an x-row (x = 0..7) moved by s = -1, 0, +1 elements: element j of the
 // result is element j + s of the row, zero outside it
@@ -247,162 +319,218 @@ __device__ __forceinline__ i32x4 window8(i32x4 r0, i32x4 r1, int d)
     return o;
 }
 
-template <bool TRAIN>
-__global__ __launch_bounds__(kTrainWaves * 64) void k_refine(RefineArgs a)
+// Weight gradient of the taps (dx, dy, dz), D0 <= dx < D1, of a layer: per tap a 16 x
+// 16 GEMM (M = output channel, N = input channel) over the 512 voxels, K = 32 voxels
+// (4 x-rows) a step, lane group kq taking row 4 ks + kq.  A = 8 voxels of the
+// gradient's channel row, held in registers for all taps (g); B = the input row at
+// the tap's (y, z) offset, read once for its three x offsets.
+template <int D0, int D1, bool FIRST>
+__device__ __forceinline__ void weight_grad(const uint16_t *xT, const i32x4 (&g)[16], int c, int lane, float *gp)
 {
-    constexpr int TPW = kTrainTPW;
-    __shared__ RefineLds L;
-    __shared__ __attribute__((aligned(16))) uint16_t s_gT[kC * kRowT];   // output gradient, [channel][voxel]
-    __shared__ __attribute__((aligned(16))) uint16_t s_xT[kC * kRowT];   // layer input, [channel][voxel]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int kq = lane >> 4, n = lane & 15;
-    for (int64_t blk = blockIdx.x; blk < a.n; blk += gridDim.x) {
-        load_input(L, a.in + blk * 2000);
-        __syncthreads();
-        f32x4 delta[TPW];
-        refine_forward<3, TPW>(L, a.P, wave, lane, delta);
-        // residual, clamp, loss gradient (lanes with output channel 0)
-        float sq = 0.0f, cnt = 0.0f;
-        if (TRAIN) {
-            for (int i = threadIdx.x; i < 512 * kC; i += blockDim.x) {
-                L.grad[0][i] = 0;
-                L.grad[1][i] = 0;
-            }
-            __syncthreads();
-        }
-        if (n == 0) {
+    const int kq = lane >> 4, n = lane & 15, dz = c / 3, dy = c % 3;
+    // row 4 ks + kq is y = 4 (ks & 1) + kq, z = ks >> 1
+    const uint16_t *base = FIRST ? xT + ((min(n, 1) * 10 + dz) * 10 + kq + dy) * 16
+                                 : xT + n * kRowA + (dz * 10 + kq + dy) * 8;
+    f32x4 acc[3];
 #pragma unroll
-            for (int t = 0; t < TPW; t++)
+    for (int d = D0; d < D1; d++) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 16; ks++) {
+        const uint16_t *p = base + ((ks >> 1) * 10 + 4 * (ks & 1)) * (FIRST ? 16 : 8);
+        i32x4 r0 = *reinterpret_cast<const i32x4 *>(p), r1 = {0, 0, 0, 0};
+        if (FIRST) {   // layer 1's input is the 10^3 grid: elements dx .. dx + 7 of its row
+            r1 = *reinterpret_cast<const i32x4 *>(p + 8);
+            if (n > 1) r0 = r1 = i32x4{0, 0, 0, 0};
+        }
+        if ((ks & 3) == 0) __builtin_amdgcn_sched_barrier(0);   // 4 rows in flight, not all 16
+#pragma unroll
+        for (int d = D0; d < D1; d++)
+            acc[d] = mfma32(g[ks], FIRST ? window8(r0, r1, d) : shift_row(r0, d - 1), acc[d]);
+    }
+#pragma unroll
+    for (int d = D0; d < D1; d++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) gp[((3 * c + d) * kC + 4 * kq + r) * kC + n] = acc[d][r];
+}
+
+// a layer's 27 taps over the 8 waves: wave w the taps of (dy, dz) pair w, and one
+// of the last pair's three on waves 1 to 3
+template <bool FIRST>
+__device__ __forceinline__ void weight_grads(const uint16_t *xT, const uint16_t *gT, int wave, int lane, float *gp)
+{
+    i32x4 g[16];
+#pragma unroll
+    for (int ks = 0; ks < 16; ks++)
+        g[ks] = *reinterpret_cast<const i32x4 *>(&gT[(lane & 15) * kRowT + 8 * (4 * ks + (lane >> 4))]);
+    weight_grad<0, 3, FIRST>(xT, g, wave, lane, gp);
+    if (wave == 1) weight_grad<0, 1, FIRST>(xT, g, 8, lane, gp);
+    else if (wave == 2) weight_grad<1, 2, FIRST>(xT, g, 8, lane, gp);
+    else if (wave == 3) weight_grad<2, 3, FIRST>(xT, g, 8, lane, gp);
+}
+
+__global__ __launch_bounds__(kTrainWaves * 64) void k_refine_train(RefineArgs a)
+{
+    constexpr int NZ = kTrainNZ;
+    __shared__ TrainLds L;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // in a scalar register
+    const int yp = wave & 3, z0 = NZ * (wave >> 2);
+    for (int64_t blk = blockIdx.x; blk < a.n; blk += gridDim.x) {
+        // opaque: what follows from the lane is formed again for each block, not kept
+        // in registers over all of them
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int kq = lane >> 4, n = lane & 15;
+        const int out = grid_out(yp, z0, lane);
+        const int vox = (n & 7) + 8 * (2 * yp + (n >> 3)) + 64 * z0;   // the lane's voxel of plane z0
+        const int voxA = (n & 7) + ((2 * yp + (n >> 3) + 1) + 10 * (z0 + 1)) * 8;
+        // everything the block reads from memory, requested together
+        const float *in = a.in + blk * 2000;
+        float Fi[2], Wi[2], ctr[NZ], tgt[NZ];
+        uint8_t msk[NZ];
+        const int u1 = min((int)threadIdx.x + 512, 999);
+        Fi[0] = in[threadIdx.x];
+        Wi[0] = in[1000 + threadIdx.x];
+        Fi[1] = in[u1];
+        Wi[1] = in[1000 + u1];
+        i32x4 w0[4], w[14];
+        load_weights0(a.P.Wf, lane, w0);
+#pragma unroll
+        for (int j = 0; j < NZ; j++) {
+            const int v = vox + 64 * j;
+            ctr[j] = in[((v & 7) + 1) + 10 * (((v >> 3) & 7) + 1) + 100 * ((v >> 6) + 1)];
+            tgt[j] = a.target[blk * 512 + v];
+            msk[j] = a.mask[blk * 512 + v];
+        }
+        if (blk == (int64_t)blockIdx.x) {   // the halos of zeros: once, the layers write the inside
+            clear_grid(L.grid);
+            i32x4 *z = reinterpret_cast<i32x4 *>(L.aT[0]);
+            for (int i = threadIdx.x; i < (int)(sizeof L.aT / 16); i += kTrainWaves * 64) z[i] = i32x4{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const int u = k ? u1 : (int)threadIdx.x;   // threads past the end store voxel 999 again
+            store_x0(L.x0, u, Fi[k], Wi[k]);
+            const int o = (u / 10) * 16 + u % 10;
+            L.x0T[o] = to_bf16(Fi[k]);
+            L.x0T[1600 + o] = to_bf16(Wi[k]);
+        }
+        f32x4 acc[NZ];
+        uint64_t on = 0;   // bit 16 l + 4 j + r: hidden layer l, channel 4 kq + r of plane j is positive
+        load_weights(a.P.Wf + kTaps * kC * kC, false, lane, w);
+        __syncthreads();
+        conv0<NZ>(L.x0, w0, yp, z0, lane, acc);
+        // (not unrolled, nor the backward loop: a block runs the code once, and
+        // fetching it takes as long as running it)
+#pragma unroll 1
+        for (int l = 0; l < kLayers - 1; l++) {
+            const f32x4 b = load_bias(a.P, l, lane);
+            if (l > 0) __syncthreads();   // every wave has read the layer's input
+            uint32_t bits = 0u;
+#pragma unroll
+            for (int j = 0; j < NZ; j++) {
+                const uint2 v = pack4(relu(acc[j], b));
+                *reinterpret_cast<uint2 *>(&L.grid[out + j * kPlane]) = v;
+                const uint16_t e[4] = {(uint16_t)v.x, (uint16_t)(v.x >> 16), (uint16_t)v.y, (uint16_t)(v.y >> 16)};
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
-                    const int vox = (wave * TPW + t) * 16 + 4 * kq + r;
-                    const float z = L.centre[vox] + delta[t][r];
-                    const float Fo = fminf(fmaxf(z, -1.0f), 1.0f);
-                    if (!TRAIN) {
-                        a.out[blk * 512 + vox] = Fo;
-                    } else {
-                        const bool m = a.mask[blk * 512 + vox] != 0;
-                        const float e = Fo - a.target[blk * 512 + vox];
-                        if (m) { sq += e * e; cnt += 1.0f; }
-                        const float g = (m && z > -1.0f && z < 1.0f) ? 2.0f * e : 0.0f;
-                        L.grad[0][vox * kC] = to_bf16(g);
-                        if (a.out) a.out[blk * 512 + vox] = Fo;
-                    }
+                    L.aT[l][(4 * kq + r) * kRowA + voxA + 80 * j] = e[r];
+                    bits |= (from_bf16(e[r]) > 0.0f ? 1u : 0u) << (4 * j + r);
                 }
-        }
-        if (!TRAIN) {
+            }
+            on |= (uint64_t)bits << (16 * l);
+            i32x4 wn[14];   // the next convolution's weights travel while this one runs
+            load_weights(l < 2 ? a.P.Wf + (size_t)(l + 2) * kTaps * kC * kC : a.P.Wt + (size_t)3 * kTaps * kC * kC,
+                         l == 2, lane, wn);
             __syncthreads();
-            continue;
+            conv16<NZ>(L.grid, w, yp, z0, lane, acc);
+#pragma unroll
+            for (int p = 0; p < 14; p++) w[p] = wn[p];
+        }
+        // residual, clamp, loss and its gradient (lanes 0-15 hold the output channel);
+        // the gradient of the 15 unused channels is zero
+        float sq = 0.0f, cnt = 0.0f;
+        f32x4 G[NZ];
+#pragma unroll
+        for (int j = 0; j < NZ; j++) G[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (kq == 0) {
+            const float b = a.P.bias[3 * kC];
+#pragma unroll
+            for (int j = 0; j < NZ; j++) {
+                const int v = vox + 64 * j;
+                const float z = ctr[j] + (acc[j][0] + b);
+                const float Fo = fminf(fmaxf(z, -1.0f), 1.0f);
+                const bool m = msk[j] != 0;
+                const float e = Fo - tgt[j];
+                if (m) { sq += e * e; cnt += 1.0f; }
+                G[j][0] = (m && z > -1.0f && z < 1.0f) ? 2.0f * e : 0.0f;
+                if (a.out) a.out[blk * 512 + v] = Fo;
+            }
         }
         // loss partial: reduce over the wave, then over the waves in wave order
-        __shared__ float red[2][kTrainWaves];
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
+        for (int o = 8; o > 0; o >>= 1) {
             sq += __shfl_xor(sq, o, 64);
             cnt += __shfl_xor(cnt, o, 64);
         }
-        if (lane == 0) { red[0][wave] = sq; red[1][wave] = cnt; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float s0 = 0.0f, s1 = 0.0f;
-            for (int w = 0; w < kTrainWaves; w++) {
-                s0 += red[0][w];
-                s1 += red[1][w];
-            }
-            a.loss_part[blk * 2] = s0;
-            a.loss_part[blk * 2 + 1] = s1;
-        }
+        if (lane == 0) { L.red[0][wave] = sq; L.red[1][wave] = cnt; }
         float *gp = a.grad_part + blk * kNP;
-        int cur = 0;
+#pragma unroll 1
         for (int l = kLayers - 1; l >= 0; l--) {
-            const uint16_t *G = L.grad[cur];
-            // bias gradient: sum of the (bf16) output gradient over the voxels, by
-            // the last wave (it has the fewest weight-gradient taps): lane = channel
-            // + 16 quarter, each quarter's 128 voxels in order, the quarters
-            // combined by a fixed butterfly
+            __syncthreads();   // the grid and the gradient rows are read
+            if (l == kLayers - 1 && threadIdx.x == 0) {
+                float s0 = 0.0f, s1 = 0.0f;
+                for (int i = 0; i < kTrainWaves; i++) {
+                    s0 += L.red[0][i];
+                    s1 += L.red[1][i];
+                }
+                a.loss_part[blk * 2] = s0;
+                a.loss_part[blk * 2 + 1] = s1;
+            }
+            // the layer's output gradient: for the data gradient's convolution and as
+            // channel rows for the weight gradient
+#pragma unroll
+            for (int j = 0; j < NZ; j++) {
+                const uint2 v = pack4(G[j]);
+                *reinterpret_cast<uint2 *>(&L.grid[out + j * kPlane]) = v;
+                const uint16_t e[4] = {(uint16_t)v.x, (uint16_t)(v.x >> 16), (uint16_t)v.y, (uint16_t)(v.y >> 16)};
+#pragma unroll
+                for (int r = 0; r < 4; r++) L.gT[(4 * kq + r) * kRowT + vox + 64 * j] = e[r];
+            }
+            __syncthreads();
+            if (l > 0) {
+                // data gradient into the layer before, masked by its ReLU
+                conv16<NZ>(L.grid, w, yp, z0, lane, acc);
+                const uint32_t m = (uint32_t)(on >> (16 * (l - 1)));
+#pragma unroll
+                for (int j = 0; j < NZ; j++)
+#pragma unroll
+                    for (int r = 0; r < 4; r++) G[j][r] = (m >> (4 * j + r)) & 1u ? acc[j][r] : 0.0f;
+                if (l > 1) load_weights(a.P.Wt + (size_t)(l - 1) * kTaps * kC * kC, true, lane, w);
+                weight_grads<false>(L.aT[l - 1], L.gT, wave, lane, gp + l * kTaps * kC * kC);
+            } else {
+                weight_grads<true>(L.x0T, L.gT, wave, lane, gp);
+            }
+            // bias gradient: sum of the (bf16) output gradient over the voxels, by the
+            // last wave: lane = channel + 16 quarter, each quarter's 128 voxels in
+            // order, the quarters combined by a fixed butterfly
             if (wave == kTrainWaves - 1) {
                 float s = 0.0f;
-                for (int v = 128 * kq; v < 128 * (kq + 1); v++) s += from_bf16(G[v * kC + n]);
+                const i32x4 *row = reinterpret_cast<const i32x4 *>(&L.gT[n * kRowT + 128 * kq]);
+#pragma unroll
+                for (int v = 0; v < 16; v++) {
+                    const i32x4 q = row[v];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        s += from_bf16((uint16_t)q[e]);
+                        s += from_bf16((uint16_t)((uint32_t)q[e] >> 16));
+                    }
+                }
                 s += __shfl_xor(s, 16, 64);
                 s += __shfl_xor(s, 32, 64);
                 if (kq == 0) gp[kNW + l * kC + n] = s;
             }
-            // weight gradient, taps split over the waves: per tap a 16 x 16 GEMM
-            // over the 512 voxels (M = output channel, N = input channel)
-            const uint16_t *X = l == 0 ? nullptr : L.act[l - 1];
-            if (l > 0) {
-                // K = 32 voxels per step (4 x-rows); lane group kq takes row 4 ks + kq:
-                // A = 8 voxels of the gradient's channel row, B = the input row at the
-                // tap's (y, z) offset, moved by its x offset
-                for (int i = threadIdx.x; i < 512 * kC; i += blockDim.x) {
-                    s_gT[(i & 15) * kRowT + (i >> 4)] = G[i];
-                    s_xT[(i & 15) * kRowT + (i >> 4)] = X[i];
-                }
-                __syncthreads();
-                for (int tap = wave; tap < kTaps; tap += kTrainWaves) {
-                    const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-                    for (int ks = 0; ks < 16; ks++) {
-                        const int row = 4 * ks + kq;   // y = row & 7, z = row >> 3
-                        const i32x4 av = *reinterpret_cast<const i32x4 *>(&s_gT[n * kRowT + 8 * row]);
-                        const int uy = (row & 7) + dy - 1, uz = (row >> 3) + dz - 1;
-                        i32x4 bv = {0, 0, 0, 0};
-                        if ((unsigned)uy < 8u && (unsigned)uz < 8u)
-                            bv = shift_row(*reinterpret_cast<const i32x4 *>(&s_xT[n * kRowT + 8 * (uy + 8 * uz)]),
-                                           dx - 1);
-                        acc = mfma32(av, bv, acc);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; r++) gp[((l * kTaps + tap) * kC + 4 * kq + r) * kC + n] = acc[r];
-                }
-            } else {
-                // layer 0's input is the 10^3 grid (4 stored channels): its copy is
-                // [channel][z][y][x, padded to 16], and a tap's 8 inputs of a row are
-                // elements dx .. dx + 7 of it (two 16-byte reads); channels past the
-                // 4 stored read zeros
-                for (int i = threadIdx.x; i < 512 * kC; i += blockDim.x) s_gT[(i & 15) * kRowT + (i >> 4)] = G[i];
-                for (int i = threadIdx.x; i < 4 * 1000; i += blockDim.x) {
-                    const int u = i >> 2, c = i & 3;
-                    s_xT[((c * 10 + u / 100) * 10 + (u / 10) % 10) * 16 + u % 10] = L.x0[i];
-                }
-                __syncthreads();
-                for (int tap = wave; tap < kTaps; tap += kTrainWaves) {
-                    const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-                    for (int ks = 0; ks < 16; ks++) {
-                        const int row = 4 * ks + kq;
-                        const i32x4 av = *reinterpret_cast<const i32x4 *>(&s_gT[n * kRowT + 8 * row]);
-                        i32x4 bv = {0, 0, 0, 0};
-                        if (n < 4) {
-                            const uint16_t *r = &s_xT[((n * 10 + (row >> 3) + dz) * 10 + (row & 7) + dy) * 16];
-                            bv = window8(*reinterpret_cast<const i32x4 *>(r), *reinterpret_cast<const i32x4 *>(r + 8), dx);
-                        }
-                        acc = mfma32(av, bv, acc);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; r++) gp[((l * kTaps + tap) * kC + 4 * kq + r) * kC + n] = acc[r];
-                }
-            }
-            if (l == 0) break;
-            // data gradient into the previous layer's output, masked by its ReLU
-            f32x4 acc[TPW];
-            conv_tiles<TPW>(L.x0, G, 1, a.P.Wt + (size_t)l * kTaps * kC * kC, true, wave, lane, acc);
-            uint16_t *Gn = L.grad[cur ^ 1];
-            const uint16_t *A = L.act[l - 1];
-#pragma unroll
-            for (int t = 0; t < TPW; t++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int vox = (wave * TPW + t) * 16 + 4 * kq + r;
-                    const bool on = from_bf16(A[vox * kC + n]) > 0.0f;
-                    Gn[vox * kC + n] = on ? to_bf16(acc[t][r]) : (uint16_t)0;
-                }
-            __syncthreads();
-            cur ^= 1;
         }
-        __syncthreads();
+        __syncthreads();   // the next block overwrites the input and the grid
     }
 }
 
@@ -512,29 +640,51 @@ __global__ void k_refine_cast(const float *master, uint16_t *Wf, uint16_t *Wt, f
     }
 }
 
-// network input of a block from the volume: F and W / max_w on the 10^3 grid
-// around it; voxels of absent neighbour blocks read F = 1, W = 0
+// The voxel blocks of a block and its 26 neighbours (index (dx + 1) + 3 (dy + 1) +
+// 9 (dz + 1); -1 where absent), one hash lookup each by the first 27 threads: the
+// 10^3 voxels around a block lie in them.
+__device__ __forceinline__ void neighbour_blocks(const HashView &h, int kx, int ky, int kz, int32_t *nb)
+{
+    if (threadIdx.x < 27) {
+        const int t = threadIdx.x;
+        nb[t] = block_of(h, find_block_direct(h, kx + t % 3 - 1, ky + t / 3 % 3 - 1, kz + t / 9 - 1));
+    }
+}
+
+// F and W / max_w of voxel u of the 10^3 grid around a block; voxels of absent
+// blocks read F = 1, W = 0
 template <int FMT>
-__global__ void k_refine_gather(HashView h, const void *sdf, const void *w, const int32_t *coords, int64_t n,
-                                float inv_max_w, float *out)
+__device__ __forceinline__ void halo_voxel(const int32_t *nb, const typename Vox<FMT>::S *S,
+                                           const typename Vox<FMT>::Wt *W, float inv_max_w, int u, float &F, float &Wf)
+{
+    const int x = u % 10 + 7, y = u / 10 % 10 + 7, z = u / 100 + 7;   // + 7: the block index is the quotient by 8
+    const int32_t p = nb[(x >> 3) + 3 * (y >> 3) + 9 * (z >> 3)];
+    F = 1.0f;
+    Wf = 0.0f;
+    if (p >= 0) {
+        const int64_t i = (int64_t)p * kBlockVox + (x & 7) + 8 * (y & 7) + 64 * (z & 7);
+        F = Vox<FMT>::to_f(S[i]);
+        Wf = Vox<FMT>::w_to_f(W[i]) * inv_max_w;
+    }
+}
+
+// network input of a block from the volume
+template <int FMT>
+__global__ __launch_bounds__(256) void k_refine_gather(HashView h, const void *sdf, const void *w,
+                                                       const int32_t *coords, int64_t n, float inv_max_w, float *out)
 {
     using V = Vox<FMT>;
-    const auto *S = (const typename V::S *)sdf;
-    const auto *Wv = (const typename V::Wt *)w;
+    __shared__ int32_t nb[27];
     for (int64_t b = blockIdx.x; b < n; b += gridDim.x) {
-        const int kx = coords[3 * b], ky = coords[3 * b + 1], kz = coords[3 * b + 2];
+        neighbour_blocks(h, coords[3 * b], coords[3 * b + 1], coords[3 * b + 2], nb);
+        __syncthreads();
         for (int u = threadIdx.x; u < 1000; u += blockDim.x) {
-            const int vx = 8 * kx - 1 + u % 10, vy = 8 * ky - 1 + (u / 10) % 10, vz = 8 * kz - 1 + u / 100;
-            const int32_t p = block_of(h, find_block_direct(h, vx >> 3, vy >> 3, vz >> 3));
-            float F = 1.0f, Wf = 0.0f;
-            if (p >= 0) {
-                const int64_t i = (int64_t)p * kBlockVox + (vx & 7) + 8 * (vy & 7) + 64 * (vz & 7);
-                F = V::to_f(S[i]);
-                Wf = V::w_to_f(Wv[i]) * inv_max_w;
-            }
+            float F, Wf;
+            halo_voxel<FMT>(nb, (const typename V::S *)sdf, (const typename V::Wt *)w, inv_max_w, u, F, Wf);
             out[b * 2000 + u] = F;
             out[b * 2000 + 1000 + u] = Wf;
         }
+        __syncthreads();
     }
 }
 
@@ -543,84 +693,65 @@ __global__ void k_refine_gather(HashView h, const void *sdf, const void *w, cons
 // volume into LDS and the refined F goes to a side buffer (half precision,
 // indexed like the voxel block array) stamped with the frame number.
 template <int FMT>
-__global__ __launch_bounds__(kInferWaves * 64) void k_refine_gated(RefineGateArgs a)
+__global__ __launch_bounds__(kInferThreads) __attribute__((amdgpu_waves_per_eu(3))) void
+k_refine_gated(RefineGateArgs a)
 {
-    constexpr int TPW = kInferTPW;
     using V = Vox<FMT>;
-    __shared__ RefineLdsInf L;
-    __shared__ int s_go;
+    __shared__ InferLds L;
+    __shared__ int32_t nb[27];
     const auto *S = (const typename V::S *)a.sdf;
     const auto *Wv = (const typename V::Wt *)a.w;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int kq = lane >> 4, n = lane & 15;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    clear_grid(L.grid);
     // the visible list (workgroup-uniform loop)
     const VisPrefix vp = vis_prefix(a.list, lane);
     for (int bi = blockIdx.x; bi < vp.total; bi += gridDim.x) {
         const VisRec rec = vis_item(a.list, vp, bi);
-        const unsigned long long key = rec.key;
         const int32_t ptr = block_of(a.h, rec.e);
         int kx, ky, kz;
-        unpack_key(key, kx, ky, kz);
+        unpack_key(rec.key, kx, ky, kz);
+        neighbour_blocks(a.h, kx, ky, kz, nb);
         // gate on the block's largest weight
-        if (threadIdx.x == 0) s_go = 0;
-        __syncthreads();
+        bool heavy = false;
         if (ptr >= 0)
-            for (int i = threadIdx.x; i < kBlockVox; i += blockDim.x)
-                if (V::w_to_f(Wv[(int64_t)ptr * kBlockVox + i]) >= a.w_threshold) s_go = 1;  // benign race
-        __syncthreads();
-        const bool skip = ptr < 0 || s_go != 0;
-        __syncthreads();                 // every thread has read s_go before it is reset
-        if (skip) continue;              // uniform over the workgroup
-        for (int u = threadIdx.x; u < 1000; u += blockDim.x) {
-            const int vx = 8 * kx - 1 + u % 10, vy = 8 * ky - 1 + (u / 10) % 10, vz = 8 * kz - 1 + u / 100;
-            const int32_t p = block_of(a.h, find_block_direct(a.h, vx >> 3, vy >> 3, vz >> 3));
-            float F = 1.0f, Wf = 0.0f;
-            if (p >= 0) {
-                const int64_t i = (int64_t)p * kBlockVox + (vx & 7) + 8 * (vy & 7) + 64 * (vz & 7);
-                F = V::to_f(S[i]);
-                Wf = V::w_to_f(Wv[i]) * a.inv_max_w;
-            }
-            uint16_t *d = &L.x0[u * 4];
-            d[0] = to_bf16(F);
-            d[1] = to_bf16(Wf);
-            d[2] = 0;
-            d[3] = 0;
-            const int x = u % 10, y = (u / 10) % 10, z = u / 100;
-            if (x >= 1 && x <= 8 && y >= 1 && y <= 8 && z >= 1 && z <= 8)
-                L.centre[(x - 1) + 8 * (y - 1) + 64 * (z - 1)] = F;
+#pragma unroll
+            for (int i = 0; i < kBlockVox; i += kInferThreads)
+                heavy |= V::w_to_f(Wv[(int64_t)ptr * kBlockVox + i + threadIdx.x]) >= a.w_threshold;
+        if (__syncthreads_or(heavy || ptr < 0)) continue;   // uniform over the workgroup
+        for (int u = threadIdx.x; u < 1000; u += kInferThreads) {
+            float F, Wf;
+            halo_voxel<FMT>(nb, S, Wv, a.inv_max_w, u, F, Wf);
+            store_x0(L.x0, u, F, Wf);
         }
-        __syncthreads();
-        f32x4 delta[TPW];
-        refine_forward<2, TPW>(L, a.P, wave, lane, delta);
-        if (n == 0) {
+        float delta[8];
+        infer_layers(L, a.P, wave, lane, delta);
+        if (lane < 16) {
 #pragma unroll
-            for (int t = 0; t < TPW; t++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int vox = (wave * TPW + t) * 16 + 4 * kq + r;
-                    const float Fo = fminf(fmaxf(L.centre[vox] + delta[t][r], -1.0f), 1.0f);
-                    a.refined[(int64_t)ptr * kBlockVox + vox] = __float2half_rn(Fo);
-                }
+            for (int j = 0; j < 8; j++) {
+                const int64_t i = (int64_t)ptr * kBlockVox + lane + 16 * wave + 64 * j;   // x + 8 y + 64 z
+                const float z = V::to_f(S[i]) + delta[j];
+                a.refined[i] = __float2half_rn(fminf(fmaxf(z, -1.0f), 1.0f));
+            }
         }
         if (threadIdx.x == 0) a.stamp[ptr] = a.frame;
-        __syncthreads();
+        __syncthreads();   // the next block overwrites nb, the input and the grid
     }
 }
 
 hipError_t launch_refine_gated(int fmt, const RefineGateArgs &a, int grid, hipStream_t st)
 {
     switch (fmt) {
-    case ITM_VOX_F32: launch_k(k_refine_gated<ITM_VOX_F32>, grid, kInferWaves * 64, st, a); break;
-    case ITM_VOX_F16: launch_k(k_refine_gated<ITM_VOX_F16>, grid, kInferWaves * 64, st, a); break;
-    default: launch_k(k_refine_gated<ITM_VOX_S16U8>, grid, kInferWaves * 64, st, a); break;
+    case ITM_VOX_F32: launch_k(k_refine_gated<ITM_VOX_F32>, grid, kInferThreads, st, a); break;
+    case ITM_VOX_F16: launch_k(k_refine_gated<ITM_VOX_F16>, grid, kInferThreads, st, a); break;
+    default: launch_k(k_refine_gated<ITM_VOX_S16U8>, grid, kInferThreads, st, a); break;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_refine(const RefineArgs &a, bool train, int grid, hipStream_t st)
 {
-    if (train) k_refine<true><<<grid, kTrainWaves * 64, 0, st>>>(a);
-    else k_refine_infer<<<grid, kInferWaves * 64, 0, st>>>(a);
+    if (train) k_refine_train<<<grid, kTrainWaves * 64, 0, st>>>(a);
+    else k_refine_infer<<<grid, kInferThreads, 0, st>>>(a);
     return hipGetLastError();
 }
 

@@ -255,3 +255,52 @@ def test_raycast_reads_refined_blocks():
     assert torch.equal(p2, p0)
     g.close()
     ref.close()
+
+
+@pytest.mark.parametrize("n", [1, 5, 769])
+def test_forward_over_grid_passes(n):
+    """Blocks beyond one pass of the grid (3 workgroups per CU) and the last of a
+    partial pass equal the oracle's, and every block equals its own forward pass."""
+    itm, torch = gpu()
+    p = _params(11)
+    inp, _, _ = _inputs(12, n)
+    ref = itm.Refiner(p)
+    x = torch.from_numpy(inp.reshape(n, 2000)).cuda()
+    out = ref.forward(x)
+    alone = torch.cat([ref.forward(x[i:i + 1]) for i in range(n)])
+    assert torch.equal(out, alone)
+    for i in {0, n // 2, n - 1}:
+        want = R.forward(inp[i].astype(np.float64), p.astype(np.float64), bf16_mode=True)[0].reshape(512)
+        assert np.abs(out[i].cpu().numpy() - want).max() < 1e-3   # as in test_forward_parity
+
+
+@pytest.mark.parametrize("n", [1, 5, 513])
+def test_gradient_over_grid_passes(n):
+    """The batch gradient is the mean of the blocks' own: float32 sums of n rows, so
+    within (n + 4) u of the rows' absolute sum."""
+    itm, torch = gpu()
+    inp, target, mask = _inputs(13, n)
+    ref = itm.Refiner(_params(14))
+    x, t, m = (torch.from_numpy(a.reshape(n, -1)).cuda() for a in (inp, target, mask))
+    g, _ = ref.gradient(x, t, m)
+    cnt = m.sum(dim=1).double()
+    rows = torch.stack([ref.gradient(x[i:i + 1], t[i:i + 1], m[i:i + 1])[0] for i in range(n)]).double()
+    rows = rows * cnt[:, None] / cnt.sum()
+    bound = (n + 4) * 2.0 ** -24 * rows.abs().sum(dim=0)
+    assert ((g.double() - rows.sum(dim=0)).abs() <= bound + 1e-30).all()
+
+
+def test_infinite_input_stays_in_its_receptive_field():
+    """An infinite halo voxel reaches what the four 3^3 layers connect it to and no
+    other voxel: the rest equals the pass without it."""
+    itm, torch = gpu()
+    inp, _, _ = _inputs(15, 1)
+    ref = itm.Refiner(_params(16))
+    x = torch.from_numpy(inp.reshape(1, 2000)).cuda()
+    base = ref.forward(x).view(8, 8, 8)
+    y = x.clone().view(2, 10, 10, 10)
+    y[0, 0, 0, 0] = float("inf")
+    out = ref.forward(y.view(1, 2000)).view(8, 8, 8)
+    far = torch.ones((8, 8, 8), dtype=torch.bool, device="cuda")
+    far[:4, :4, :4] = False   # layer 1 takes the corner to voxel 0, layers 2-4 three voxels on
+    assert torch.equal(out[far], base[far])
