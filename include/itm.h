@@ -98,7 +98,8 @@ itm_scene *itm_scene_create_ex(float voxel_size, float mu, int32_t max_w, int64_
 /* Free every device and host resource of the scene -- the hash table and the
  * voxel block array of section "Hash Table and Hashing Function" / "Voxel Block
  * Array", the visible list, the search-range bins, the tracker's, colour's,
- * refiner's and swapping's buffers (synchronises its stream).  NULL is ignored. */
+ * refiner's and swapping's buffers, the exports' staging (synchronises its
+ * stream).  NULL is ignored. */
 void itm_scene_destroy(itm_scene *scene);
 
 /* Replace the scene's HIP stream (hipStream_t, may be NULL). */
@@ -169,7 +170,9 @@ itm_status itm_expected_depths(itm_scene *scene, const itm_intrinsics *K, const 
  *           W as a float, voxel order lx + 8 ly + 64 lz
  *   capacity  blocks the buffers hold; ITM_ERR_ARG when smaller than the count
  *   n_blocks  HOST int64 out: number of allocated blocks
- * Synchronises the stream. */
+ * The first export of voxels or colour allocates 32 MiB of staging on the device
+ * and 32 MiB pinned on the host, kept by the scene; up to 8 host threads fill the
+ * buffers during the call.  Synchronises the stream. */
 itm_status itm_export_blocks(itm_scene *scene, int32_t *coords, float *sdf, float *w,
                              int64_t capacity, int64_t *n_blocks);
 

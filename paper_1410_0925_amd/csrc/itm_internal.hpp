@@ -204,6 +204,7 @@ struct Vox<ITM_VOX_F32> {
     using Wt = float;
     static constexpr int bytes = 8;
     __device__ static float to_f(float s) { return s; }
+    __device__ static float export_f(float s) { return s; }
     __device__ static float from_f(float f) { return f; }
     __device__ static float w_to_f(float w) { return w; }
     __device__ static float w_from_f(float w) { return w; }
@@ -215,6 +216,7 @@ struct Vox<ITM_VOX_F16> {
     using Wt = __half;
     static constexpr int bytes = 4;
     __device__ static float to_f(__half s) { return __half2float(s); }
+    __device__ static float export_f(__half s) { return __half2float(s); }
     __device__ static __half from_f(float f) { return __float2half_rn(f); }
     __device__ static float w_to_f(__half w) { return __half2float(w); }
     __device__ static __half w_from_f(float w) { return __float2half_rn(w); }
@@ -226,6 +228,7 @@ struct Vox<ITM_VOX_S16U8> {
     using Wt = uint8_t;
     static constexpr int bytes = 3;
     __device__ static float to_f(int16_t s) { return (float)s * (1.0f / 32767.0f); }
+    __device__ static float export_f(int16_t s) { return (float)s / 32767.0f; }   // the exported value: correctly rounded
     __device__ static int16_t from_f(float f)
     {
         float q = rintf(f * 32767.0f);
@@ -438,6 +441,26 @@ hipError_t launch_import_voxels(int fmt, const int32_t *entry, const float *in_s
                                 void *sdf, void *w, uchar4 *clr, hipStream_t st);
 hipError_t launch_integrate(int fmt, const FuseArgs &a, int grid, hipStream_t st);
 hipError_t launch_raycast(int fmt, const RaycastArgs &a, hipStream_t st);
+// sorting n block keys (with an entry each): scratch, and the allocated blocks in
+// key order (x, y, z)
+struct SortedBlocks {
+    unsigned long long *key, *key2;   // [n] order-preserving keys
+    int32_t *ent, *ent2;              // [n] their entries
+    int32_t *out_ent;                 // [n] entries in key order
+    int32_t *coords;                  // [n][3] (x, y, z) in key order
+    int32_t *count;                   // keys collected
+};
+constexpr int kSortTile = 4096;
+// the table's n keys: out_ent and coords
+hipError_t launch_sort_blocks(const HashView &h, int32_t n, const SortedBlocks &b, hipStream_t st);
+// *dup set to 1 where two of the n coordinates are equal, else 0 (scratch: key, key2, ent, ent2)
+hipError_t launch_find_repeats(const int32_t *coords, int32_t n, const SortedBlocks &b, int32_t *dup, hipStream_t st);
+// voxels of blocks[0..n) as floats, either output may be null
+hipError_t launch_export_floats(int fmt, const void *sdf, const void *w, const int32_t *blocks, int64_t n,
+                                float *out_sdf, float *out_w, hipStream_t st);
+// *first lowered to the index (+ base) of the first of n voxels that is no valid state
+hipError_t launch_import_check(const float *sdf, const float *w, int64_t n, int64_t base, float max_w,
+                               unsigned long long *first, hipStream_t st);
 hipError_t launch_export_gather(int fmt, const void *sdf, const void *w, const int32_t *blocks, int64_t n,
                                 void *out_sdf, void *out_w, hipStream_t st);
 hipError_t launch_export_colour(const uchar4 *clr, const int32_t *blocks, int64_t n, uchar4 *out, hipStream_t st);
