@@ -1502,7 +1502,10 @@ IcpArgs icp_args(const TrackBufs &b, const float *depth, const itm_intrinsics *K
         for (int j = 0; j < 3; j++) a.Rr[3 * i + j] = (float)T_ref[4 * i + j];
         a.tr[i] = (float)T_ref[4 * i + 3];
     }
-    a.dist = dist;
+    // sqrtf(x) > dist as a test of x: the largest x that fails it
+    a.dist2 = dist * dist;
+    while (std::sqrt(a.dist2) > dist) a.dist2 = std::nextafter(a.dist2, 0.0f);
+    for (float x; x = std::nextafter(a.dist2, INFINITY), std::isfinite(x) && std::sqrt(x) <= dist;) a.dist2 = x;
     a.pose = b.pose;
     a.stop = b.flags + level;   // cleared by k_track_init; set only by steps that update
     a.steps = nullptr;

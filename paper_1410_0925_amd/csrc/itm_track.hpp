@@ -26,7 +26,7 @@ struct IcpArgs {
     int32_t W, H;                // input and reference size
     const float4 *V, *N;         // reference maps, world frame, w > 0 = hit
     float Rr[9], tr[3];          // reference pose (camera -> world)
-    float dist;                  // pairing distance
+    float dist2;                 // the largest number whose rounded square root is <= the pairing distance
     double *pose;                // current estimate, device double[16]; moved by the step
     int32_t *stop;               // the level's stop flag (read even when update == 0)
     int32_t *steps;              // steps taken, or nullptr (then update == 0)

@@ -82,6 +82,35 @@ def test_sums_match_the_oracle(size):
             compare_systems(g, o)
 
 
+@pytest.mark.parametrize("dist", [0.02, 0.05, 0.1, 0.3, 1.0])
+def test_pairs_at_the_distance_threshold(dist):
+    # reference points within a few units in the last place of the threshold: the
+    # pairs are those whose float32 distance, rounded, is not above it (the sum and
+    # its root are correctly rounded on either side, so the counts are equal)
+    itm, torch = gpu()
+    f = np.float32
+    W, H, K = 64, 32, (50.0, 50.0, 31.5, 15.5)
+    rng = np.random.default_rng(int(1000 * dist))
+    depth = np.full((H, W), 2.0, f)
+    u, v = np.meshgrid(np.arange(W, dtype=f), np.arange(H, dtype=f))
+    P = np.stack([f(2) * (u - f(K[2])) / f(K[0]), f(2) * (v - f(K[3])) / f(K[1]), depth], -1)
+    off = rng.normal(size=(H, W, 3))
+    off /= np.linalg.norm(off, axis=-1, keepdims=True)
+    off *= float(f(dist)) * (1 + rng.integers(-12, 13, (H, W, 1)) * 2.0**-23)
+    V = np.ones((H, W, 4), f)
+    V[..., :3] = (P.astype(np.float64) - off).astype(f)
+    N = np.ones((H, W, 4), f)
+    N[..., :3] = [0, 0, -1]
+    e = P - V[..., :3]
+    want = int((np.sqrt(e[..., 0] * e[..., 0] + e[..., 1] * e[..., 1] + e[..., 2] * e[..., 2]) <= f(dist)).sum())
+    assert 0.2 * W * H < want < 0.8 * W * H
+    d_g, V_g, N_g = upload(torch, depth, V, N)
+    sc = itm.Scene(0.01, 0.04, 100, 1 << 12, 1 << 10)
+    print(f"case: threshold {dist}", flush=True)
+    g = sc.icp_system(d_g, K + (W, H), 0, V_g, N_g, np.eye(4), np.eye(4), dist)
+    assert g[28] == want
+
+
 def test_tracks_a_known_motion_like_the_oracle():
     itm, torch = gpu()
     W, H, K = 160, 120, (140.0, 140.0, 79.5, 59.5)
