@@ -340,8 +340,10 @@ itm_status itm_track_noalloc(itm_scene *scene, const float *depth, const itm_int
 /*  - swap out: of the device blocks not visible in the frame with nothing to */
 /*    merge, the first swap_out in key order move to the host (a host voxel   */
 /*    block per hash entry, kept by the library) and free their device block.  */
-/* Transfers go through fixed-size buffers (pinned on the host) of            */
-/* max(swap_in, swap_out) blocks; each frame synchronises the stream twice.   */
+/* The host copies are in pinned memory (8 MiB or less at a time as they come  */
+/* to be needed, kept until the scene is destroyed; ITM_ERR_OOM, with the frame */
+/* fused and nothing moved, when there is no more), which the device reads and */
+/* writes directly; each frame synchronises the stream twice.                  */
 /* The raycast sees the blocks on the device only; itm_export_blocks returns    */
 /* every block wherever it is (merged when both copies exist).  Call before   */
 /* the first frame; not with colour, a refiner or itm_import_blocks            */

@@ -411,6 +411,19 @@ struct alignas(16) SwapRec {
     int32_t e;
     int32_t pad;
 };
+constexpr int kSwapPasses = 4;             // of the choice: 12 bits of the 48-bit key each
+constexpr int kSwapHistWords = 2 * kSwapPasses << 12;
+constexpr int kSwapChooseWgs = 64;         // per list
+constexpr int kSwapMoveWgs = 128;
+constexpr int kSwapChunk = 2048;           // host copies per allocation
+struct SwapCnt {
+    unsigned long long cand;   // candidates: swap in | swap out << 32
+    uint32_t chosen[2];        // places drawn in the lists of the chosen
+};
+struct SwapSel {               // of the cap-th smallest key: its digits so far, and its
+    unsigned long long prefix; // place (from 1) among the keys that share them
+    uint32_t rem;
+};
 struct SwapScanArgs {
     HashView h;
     const uint32_t *stamp;
@@ -418,21 +431,37 @@ struct SwapScanArgs {
     const uint8_t *onhost;
     int64_t n_entries;
     SwapRec *in_list, *out_list;
-    int32_t *cnt;             // [2]: in, out (cleared by the host)
+    SwapCnt *cnt;             // this frame's, zero
+    uint32_t *hist;           // [kSwapHistWords], cleared here
     PoolView pool;
+};
+struct SwapSelArgs {
+    const SwapRec *list[2];   // candidates: in, out
+    int32_t cap[2];
+    SwapCnt *cnt, *cnt_next;  // this frame's, and the next one's (zeroed here)
+    uint32_t *hist;           // digit counts: [list][pass][4096]
+    SwapSel *sel;             // [list][pass]
+    int32_t *chosen[2];       // entries: in, out
+    int32_t *moves;           // [2], host memory: how many of each
 };
 struct SwapMoveArgs {
     HashView h;
     void *sdf, *w;            // the device voxel blocks
-    void *xfer_sdf, *xfer_w;  // device transfer buffer, block i at i * 512 voxels
-    const int32_t *entries;   // [n]
-    int32_t n;
+    const int32_t *chosen[2];
+    int32_t n_in, n_out;
     uint8_t *onhost;
+    int32_t *slot_of;         // per entry, the slot of its host copy
+    uint8_t *const *chunks;   // host memory of the slots, kSwapChunk each
+    int32_t *free_ring;       // free slots, first in first out
+    int64_t ring_head, ring_tail, ring_size;
+    int32_t n_free;           // free slots before this frame; further outs take
+    int32_t slot_next;        // new ones from here
     float max_w;
     PoolView pool;
 };
 hipError_t launch_swap_scan(const SwapScanArgs &a, hipStream_t st);
-hipError_t launch_swap_move(int fmt, bool out, const SwapMoveArgs &a, hipStream_t st);
+hipError_t launch_swap_choose(const SwapSelArgs &a, hipStream_t st);
+hipError_t launch_swap_move(int fmt, const SwapMoveArgs &a, hipStream_t st);
 hipError_t launch_swap_init(int32_t *stack, int32_t n_blocks, int32_t *top, int32_t *blk, uint8_t *onhost,
                             int64_t n_entries, hipStream_t st);
 hipError_t launch_alloc(const FuseArgs &a, hipStream_t st);

@@ -126,14 +126,22 @@ struct itm_scene {
     int32_t *pool_top = nullptr;      // [2]: stack top, then the scan counts' home (unused)
     unsigned long long *pool_noblock = nullptr;
     SwapRec *swap_in_list = nullptr, *swap_out_list = nullptr;   // [n_entries] each
-    int32_t *swap_cnt = nullptr;      // [2]
+    SwapCnt *swap_cnt = nullptr;      // [2], one per frame parity
+    uint32_t *swap_hist = nullptr;    // [kSwapHistWords]
+    SwapSel *swap_sel = nullptr;      // [2][kSwapPasses]
+    int32_t *swap_chosen = nullptr;   // [swap_in_cap + swap_out_cap] entries that move: in, then out
+    int32_t *swap_moves = nullptr;    // [2] how many, pinned
+    int32_t swap_parity = 0;
     int32_t swap_in_cap = 0, swap_out_cap = 0;
-    void *xfer_sdf = nullptr, *xfer_w = nullptr;   // device transfer buffer, max(in, out) blocks
-    int32_t *xfer_entries = nullptr;
-    uint8_t *xfer_host = nullptr;     // pinned host transfer buffer: in blocks, then out blocks
-    std::vector<int32_t> host_slot;   // [n_entries] slot of the entry's host copy, -1 none
-    std::vector<uint8_t> host_data;   // host voxel blocks (storage form), one slot each
-    std::vector<int32_t> host_free;   // free slots
+    // the host copies: pinned voxel blocks (storage form, F then W), one slot each.
+    // A slot belongs to one entry or is in the ring of free slots, so there are
+    // never more than entries.
+    std::vector<uint8_t *> host_chunks;   // kSwapChunk slots each
+    uint8_t **chunk_tab = nullptr;    // the same pointers, on the device
+    int32_t *slot_of = nullptr;       // [n_entries] slot of the entry's host copy (where onhost)
+    int32_t *free_ring = nullptr;     // [n_entries] free slots
+    int64_t ring_head = 0, ring_tail = 0;
+    int32_t slot_next = 0;            // slots handed out so far
     int64_t swapped_in_last = 0, swapped_out_last = 0, swapped_in_total = 0, swapped_out_total = 0;
 
     bool prof = false;
@@ -211,9 +219,11 @@ void release(itm_scene *sc)
         if (e) (void)hipEventDestroy(e);
     for (void *p : {(void *)sc->blk, (void *)sc->onhost, (void *)sc->pool_stack, (void *)sc->pool_top,
                     (void *)sc->pool_noblock, (void *)sc->swap_in_list, (void *)sc->swap_out_list,
-                    (void *)sc->swap_cnt, sc->xfer_sdf, sc->xfer_w, (void *)sc->xfer_entries})
+                    (void *)sc->swap_cnt, (void *)sc->swap_hist, (void *)sc->swap_sel, (void *)sc->swap_chosen,
+                    (void *)sc->chunk_tab, (void *)sc->slot_of, (void *)sc->free_ring})
         (void)hipFree(p);
-    if (sc->xfer_host) (void)hipHostFree(sc->xfer_host);
+    if (sc->swap_moves) (void)hipHostFree(sc->swap_moves);
+    for (uint8_t *p : sc->host_chunks) (void)hipHostFree(p);
     delete sc;
 }
 
@@ -604,34 +614,35 @@ itm_status refine_visible(itm_scene *sc)
     return ITM_OK;
 }
 
-// the key of a swap record as (x, y, z), for the host's key order
-void swap_key(const SwapRec &r, int &x, int &y, int &z)
+// pinned host memory for the first n_slots slots of host copies
+itm_status grow_host_copies(itm_scene *sc, int64_t n_slots)
 {
-    x = (int16_t)(r.key & 0xffffu);
-    y = (int16_t)((r.key >> 16) & 0xffffu);
-    z = (int16_t)((r.key >> 32) & 0xffffu);
+    const size_t bytes = (sdf_elem(sc->fmt) + w_elem(sc->fmt)) * kBlockVox * (size_t)kSwapChunk;
+    const size_t had = sc->host_chunks.size(), want = (size_t)((n_slots + kSwapChunk - 1) / kSwapChunk);
+    if (want <= had) return ITM_OK;
+    while (sc->host_chunks.size() < want) {
+        uint8_t *p = nullptr;
+        if (hipHostMalloc((void **)&p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            break;
+        }
+        sc->host_chunks.push_back(p);
+    }
+    const size_t got = sc->host_chunks.size();
+    if (got > had)   // from the vector's memory, complete on return
+        HIP_TRY(hipMemcpy(sc->chunk_tab + had, sc->host_chunks.data() + had, sizeof(uint8_t *) * (got - had),
+                          hipMemcpyHostToDevice));
+    return got < want ? fail(ITM_ERR_OOM, "pinned host copies of %lld blocks", (long long)n_slots) : ITM_OK;
 }
 
-bool swap_key_less(const SwapRec &a, const SwapRec &b)
-{
-    int ax, ay, az, bx, by, bz;
-    swap_key(a, ax, ay, az);
-    swap_key(b, bx, by, bz);
-    if (ax != bx) return ax < bx;
-    if (ay != by) return ay < by;
-    return az < bz;
-}
-
-// After a frame's integration (section "Swapping"): the candidates are found
-// on the device; the host takes, in key order, up to swap_in_cap host copies to
-// merge into their device blocks and up to swap_out_cap device blocks that were
-// not visible in the frame (and have nothing to merge) to move to the host.
-// Two host synchronisations per frame.
+// After a frame's integration (section "Swapping"): of the candidates, found on
+// the device, up to swap_in_cap host copies merge into their device blocks and
+// up to swap_out_cap device blocks that were not visible in the frame (and have
+// nothing to merge) move to the host, the first in key order.  Two host
+// synchronisations per frame: after the choice, when the host makes room for the
+// copies, and after the moves.
 itm_status swap_frame(itm_scene *sc)
 {
-    const size_t es = sdf_elem(sc->fmt), ew = w_elem(sc->fmt);
-    const size_t blk_bytes = (es + ew) * kBlockVox;
-    HIP_TRY(hipMemsetAsync(sc->swap_cnt, 0, sizeof(int32_t) * 2, sc->stream));
     SwapScanArgs sa;
     sa.h = hash_view(sc);
     sa.stamp = sc->vis_stamp;
@@ -640,84 +651,52 @@ itm_status swap_frame(itm_scene *sc)
     sa.n_entries = sc->n_entries;
     sa.in_list = sc->swap_in_list;
     sa.out_list = sc->swap_out_list;
-    sa.cnt = sc->swap_cnt;
+    sa.cnt = sc->swap_cnt + sc->swap_parity;
+    sa.hist = sc->swap_hist;
     sa.pool = pool_view(sc);
+    SwapSelArgs se;
+    se.list[0] = sc->swap_in_list;
+    se.list[1] = sc->swap_out_list;
+    se.cap[0] = sc->swap_in_cap;
+    se.cap[1] = sc->swap_out_cap;
+    se.cnt = sa.cnt;
+    se.cnt_next = sc->swap_cnt + (sc->swap_parity ^ 1);
+    se.hist = sc->swap_hist;
+    se.sel = sc->swap_sel;
+    se.chosen[0] = sc->swap_chosen;
+    se.chosen[1] = sc->swap_chosen + sc->swap_in_cap;
+    se.moves = sc->swap_moves;
     HIP_TRY(launch_swap_scan(sa, sc->stream));
-    int32_t cnt[2];
-    HIP_TRY(hipMemcpyAsync(cnt, sc->swap_cnt, sizeof cnt, hipMemcpyDeviceToHost, sc->stream));
+    HIP_TRY(launch_swap_choose(se, sc->stream));
     HIP_TRY(hipStreamSynchronize(sc->stream));
-    std::vector<SwapRec> in(cnt[0]), out(cnt[1]);
-    if (cnt[0]) HIP_TRY(hipMemcpyAsync(in.data(), sc->swap_in_list, sizeof(SwapRec) * cnt[0], hipMemcpyDeviceToHost, sc->stream));
-    if (cnt[1]) HIP_TRY(hipMemcpyAsync(out.data(), sc->swap_out_list, sizeof(SwapRec) * cnt[1], hipMemcpyDeviceToHost, sc->stream));
-    HIP_TRY(hipStreamSynchronize(sc->stream));
-    std::sort(in.begin(), in.end(), swap_key_less);
-    std::sort(out.begin(), out.end(), swap_key_less);
-    const int32_t n_in = std::min<int32_t>(cnt[0], sc->swap_in_cap);
-    const int32_t n_out = std::min<int32_t>(cnt[1], sc->swap_out_cap);
-    const int32_t xcap = std::max(sc->swap_in_cap, sc->swap_out_cap);
+    sc->swap_parity ^= 1;
+    const int32_t n_in = sc->swap_moves[0], n_out = sc->swap_moves[1];
     SwapMoveArgs ma;
     ma.h = sa.h;
     ma.sdf = sc->sdf;
     ma.w = sc->w;
-    ma.xfer_sdf = sc->xfer_sdf;
-    ma.xfer_w = sc->xfer_w;
-    ma.entries = sc->xfer_entries;
+    ma.chosen[0] = se.chosen[0];
+    ma.chosen[1] = se.chosen[1];
+    ma.n_in = n_in;
+    ma.n_out = n_out;
     ma.onhost = sc->onhost;
+    ma.slot_of = sc->slot_of;
+    ma.chunks = sc->chunk_tab;
+    ma.free_ring = sc->free_ring;
+    ma.ring_head = sc->ring_head;
+    ma.ring_tail = sc->ring_tail;
+    ma.ring_size = sc->n_entries;
+    ma.n_free = (int32_t)(sc->ring_tail - sc->ring_head);
+    ma.slot_next = sc->slot_next;
     ma.max_w = (float)sc->max_w;
     ma.pool = sa.pool;
-    std::vector<int32_t> ents;
-    // swap in: host copies into the transfer buffer (F then W parts, as on the
-    // device), then merged into the device blocks
-    if (n_in) {
-        uint8_t *hs = sc->xfer_host, *hw = sc->xfer_host + es * kBlockVox * (size_t)xcap;
-        ents.resize(n_in);
-        for (int32_t i = 0; i < n_in; i++) {
-            const int32_t e = in[i].e;
-            const int32_t slot = sc->host_slot[e];
-            const uint8_t *src = sc->host_data.data() + (size_t)slot * blk_bytes;
-            std::memcpy(hs + es * kBlockVox * (size_t)i, src, es * kBlockVox);
-            std::memcpy(hw + ew * kBlockVox * (size_t)i, src + es * kBlockVox, ew * kBlockVox);
-            ents[i] = e;
-        }
-        HIP_TRY(hipMemcpyAsync(sc->xfer_sdf, hs, es * kBlockVox * (size_t)n_in, hipMemcpyHostToDevice, sc->stream));
-        HIP_TRY(hipMemcpyAsync(sc->xfer_w, hw, ew * kBlockVox * (size_t)n_in, hipMemcpyHostToDevice, sc->stream));
-        HIP_TRY(hipMemcpyAsync(sc->xfer_entries, ents.data(), sizeof(int32_t) * n_in, hipMemcpyHostToDevice,
-                               sc->stream));
-        ma.n = n_in;
-        HIP_TRY(launch_swap_move(sc->fmt, false, ma, sc->stream));
-        HIP_TRY(hipStreamSynchronize(sc->stream));   // the buffers are reused below
-        for (int32_t i = 0; i < n_in; i++) {
-            sc->host_free.push_back(sc->host_slot[in[i].e]);
-            sc->host_slot[in[i].e] = -1;
-        }
-    }
-    // swap out: device blocks through the transfer buffer to host slots
-    if (n_out) {
-        ents.resize(n_out);
-        for (int32_t i = 0; i < n_out; i++) ents[i] = out[i].e;
-        HIP_TRY(hipMemcpyAsync(sc->xfer_entries, ents.data(), sizeof(int32_t) * n_out, hipMemcpyHostToDevice,
-                               sc->stream));
-        ma.n = n_out;
-        HIP_TRY(launch_swap_move(sc->fmt, true, ma, sc->stream));
-        uint8_t *hs = sc->xfer_host, *hw = sc->xfer_host + es * kBlockVox * (size_t)xcap;
-        HIP_TRY(hipMemcpyAsync(hs, sc->xfer_sdf, es * kBlockVox * (size_t)n_out, hipMemcpyDeviceToHost, sc->stream));
-        HIP_TRY(hipMemcpyAsync(hw, sc->xfer_w, ew * kBlockVox * (size_t)n_out, hipMemcpyDeviceToHost, sc->stream));
-        HIP_TRY(hipStreamSynchronize(sc->stream));
-        for (int32_t i = 0; i < n_out; i++) {
-            int32_t slot;
-            if (!sc->host_free.empty()) {
-                slot = sc->host_free.back();
-                sc->host_free.pop_back();
-            } else {
-                slot = (int32_t)(sc->host_data.size() / blk_bytes);
-                sc->host_data.resize(sc->host_data.size() + blk_bytes);
-            }
-            uint8_t *dst = sc->host_data.data() + (size_t)slot * blk_bytes;
-            std::memcpy(dst, hs + es * kBlockVox * (size_t)i, es * kBlockVox);
-            std::memcpy(dst + es * kBlockVox, hw + ew * kBlockVox * (size_t)i, ew * kBlockVox);
-            sc->host_slot[out[i].e] = slot;
-        }
-    }
+    const int32_t reused = std::min(n_out, ma.n_free);
+    if (itm_status st = grow_host_copies(sc, (int64_t)sc->slot_next + (n_out - reused))) return st;
+    HIP_TRY(launch_swap_move(sc->fmt, ma, sc->stream));
+    HIP_TRY(hipStreamSynchronize(sc->stream));
+    sc->ring_head += reused;
+    sc->ring_tail += n_in;
+    sc->slot_next += n_out - reused;
     sc->swapped_in_last = n_in;
     sc->swapped_out_last = n_out;
     sc->swapped_in_total += n_in;
@@ -1143,12 +1122,14 @@ itm_status itm_export_blocks(itm_scene *sc, int32_t *coords, float *sdf, float *
     }
     // with swapping a block's data may sit on the device, on the host, or both
     // (a host copy not merged yet: exported merged, as the swap-in would merge it)
-    std::vector<int32_t> ent(n), dblk(sc->n_entries);
+    std::vector<int32_t> ent(n), dblk(sc->n_entries), slots(sc->n_entries);
     std::vector<uint8_t> onh(sc->n_entries);
     HIP_TRY(hipMemcpyAsync(ent.data(), b.out_ent, sizeof(int32_t) * n, hipMemcpyDeviceToHost, sc->stream));
     HIP_TRY(hipMemcpyAsync(dblk.data(), sc->blk, sizeof(int32_t) * sc->n_entries, hipMemcpyDeviceToHost,
                            sc->stream));
     HIP_TRY(hipMemcpyAsync(onh.data(), sc->onhost, sc->n_entries, hipMemcpyDeviceToHost, sc->stream));
+    HIP_TRY(hipMemcpyAsync(slots.data(), sc->slot_of, sizeof(int32_t) * sc->n_entries, hipMemcpyDeviceToHost,
+                           sc->stream));
     HIP_TRY(hipStreamSynchronize(sc->stream));
     // the device blocks' voxels, packed on the device in export order, then one copy
     const size_t es = sdf_elem(sc->fmt), ew = w_elem(sc->fmt);
@@ -1176,8 +1157,9 @@ itm_status itm_export_blocks(itm_scene *sc, int32_t *coords, float *sdf, float *
     const size_t blk_bytes = (es + ew) * kBlockVox;
     for (int64_t i = 0; i < n; i++) {
         const size_t src = (size_t)i * kBlockVox;
-        const int32_t db = dblk[ent[i]], slot = onh[ent[i]] ? sc->host_slot[ent[i]] : -1;
-        const uint8_t *host = slot >= 0 ? sc->host_data.data() + (size_t)slot * blk_bytes : nullptr;
+        const int32_t db = dblk[ent[i]], slot = onh[ent[i]] ? slots[ent[i]] : -1;
+        const uint8_t *host =
+            slot >= 0 ? sc->host_chunks[slot / kSwapChunk] + (size_t)(slot % kSwapChunk) * blk_bytes : nullptr;
         for (int l = 0; l < kBlockVox; l++) {
             float f = 1.0f, wf = 0.0f;
             if (db >= 0) {   // the device copy
@@ -1225,7 +1207,6 @@ itm_status itm_scene_enable_swapping(itm_scene *sc, int64_t device_blocks, int32
     sc->vba_cap = device_blocks;
     const int64_t n_vox = device_blocks * kBlockVox;
     const size_t es = sdf_elem(sc->fmt), ew = w_elem(sc->fmt);
-    const int32_t xcap = std::max(1, std::max(swap_in, swap_out));
     if (itm_status st = dev_alloc(&sc->sdf, es * n_vox, "sdf")) return st;
     if (itm_status st = dev_alloc(&sc->w, ew * n_vox, "weights")) return st;
     if (dev_alloc((void **)&sc->blk, sizeof(int32_t) * sc->n_entries, "entry blocks") ||
@@ -1235,13 +1216,16 @@ itm_status itm_scene_enable_swapping(itm_scene *sc, int64_t device_blocks, int32
         dev_alloc((void **)&sc->pool_noblock, sizeof(unsigned long long), "pool misses") ||
         dev_alloc((void **)&sc->swap_in_list, sizeof(SwapRec) * sc->n_entries, "swap-in candidates") ||
         dev_alloc((void **)&sc->swap_out_list, sizeof(SwapRec) * sc->n_entries, "swap-out candidates") ||
-        dev_alloc((void **)&sc->swap_cnt, sizeof(int32_t) * 2, "swap counts") ||
-        dev_alloc(&sc->xfer_sdf, es * kBlockVox * (size_t)xcap, "transfer sdf") ||
-        dev_alloc(&sc->xfer_w, ew * kBlockVox * (size_t)xcap, "transfer weights") ||
-        dev_alloc((void **)&sc->xfer_entries, sizeof(int32_t) * xcap, "transfer entries"))
+        dev_alloc((void **)&sc->swap_cnt, sizeof(SwapCnt) * 2, "swap counts") ||
+        dev_alloc((void **)&sc->swap_hist, sizeof(uint32_t) * kSwapHistWords, "swap digit counts") ||
+        dev_alloc((void **)&sc->swap_sel, sizeof(SwapSel) * 2 * kSwapPasses, "swap choice") ||
+        dev_alloc((void **)&sc->swap_chosen, sizeof(int32_t) * ((size_t)swap_in + swap_out), "swap entries") ||
+        dev_alloc((void **)&sc->chunk_tab, sizeof(uint8_t *) * (sc->n_entries / kSwapChunk + 1), "host copy table") ||
+        dev_alloc((void **)&sc->slot_of, sizeof(int32_t) * sc->n_entries, "host slots") ||
+        dev_alloc((void **)&sc->free_ring, sizeof(int32_t) * sc->n_entries, "free host slots"))
         return ITM_ERR_OOM;
-    if (hipHostMalloc((void **)&sc->xfer_host, (es + ew) * kBlockVox * (size_t)xcap) != hipSuccess)
-        return fail(ITM_ERR_OOM, "pinned transfer buffer of %d blocks", xcap);
+    if (hipHostMalloc((void **)&sc->swap_moves, sizeof(int32_t) * 2) != hipSuccess)
+        return fail(ITM_ERR_OOM, "pinned swap counts");
     hipError_t e = launch_init(sc->buckets, sc->head, sc->n_buckets, sc->excess, sc->n_excess, sc->vis_stamp,
                                sc->n_entries, sc->set, 2 * sc->set_size, sc->occ,
                                sc->occ_words + kMacroWords, sc->cnt, sc->fmt, sc->sdf, sc->w,
@@ -1250,11 +1234,9 @@ itm_status itm_scene_enable_swapping(itm_scene *sc, int64_t device_blocks, int32
         e = launch_swap_init(sc->pool_stack, (int32_t)device_blocks, sc->pool_top, sc->blk, sc->onhost,
                              sc->n_entries, sc->stream);
     if (e == hipSuccess) e = hipMemsetAsync(sc->pool_noblock, 0, sizeof(unsigned long long), sc->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(sc->swap_cnt, 0, sizeof(SwapCnt) * 2, sc->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(sc->stream);
     if (e != hipSuccess) return fail(ITM_ERR_HIP, "swapping set-up failed: %s", hipGetErrorString(e));
-    sc->host_slot.assign(sc->n_entries, -1);
-    sc->host_data.clear();
-    sc->host_free.clear();
     sc->swap_in_cap = swap_in;
     sc->swap_out_cap = swap_out;
     sc->swap = true;

@@ -111,3 +111,25 @@ def test_device_pool_without_transfers():
         o.integrate(st.depth[f], st.intrinsics, st.T_wc[f])
     compare_volumes(g.export(), o.export(), cands=o.export_candidates())
     g.close()
+
+
+@pytest.mark.parametrize("fmt,swap_in,swap_out", [("f32", 1, 1), ("f16", 33, 1 << 20), ("f16", 500, 37),
+                                                  ("s16u8", 500, 43)])
+def test_the_choice_at_its_edges(fmt, swap_in, swap_out):
+    """The blocks that move, over transfers of one block, of exactly as many
+    blocks as there are candidates, of fewer and of more (so that either list is
+    taken whole or chosen from), with a number of entries that is no multiple of
+    a thread's four: the numbers moved are the oracle's in every frame, and the
+    volume is its volume.  Bars as above; half precision rounds F at every fusion
+    and merge, by 2^-11 relative at most."""
+    itm, torch = gpu()
+    st = make_stream("tiny", n_frames=40)
+    st.params = dict(st.params, n_excess=st.params["n_excess"] + 1)
+    print(f"case: tiny 40 frames, {fmt}, transfers of {swap_in} and {swap_out} blocks", flush=True)
+    g, o, _ = run_both(st, 40, 4096, swap_in, swap_out, fmt=fmt)
+    s = g.swap_stats()
+    assert s["swapped_in_total"] > 0 and s["swapped_out_total"] > 0
+    tol = {"f32": 1e-5, "f16": lambda W: 2.0 ** -11 * (np.asarray(W, np.float64) + 1) + 1e-5,
+           "s16u8": lambda W: (0.5 / 32767 + 4 * 2.0 ** -23) * (np.asarray(W, np.float64) + 1) + 1e-6}[fmt]
+    compare_volumes(g.export(), o.export(), tol=tol, cands=o.export_candidates())
+    g.close()
