@@ -723,10 +723,11 @@ itm_status integrate_frame(itm_scene *sc, const float *depth, const uchar4 *rgbx
     }
     {
         ProfScope ps(sc, 1);
-        // 5 workgroups per CU: every wave resident at once (about one block each at
-        // VGA), looping over its share of the list when more are listed; a
-        // multiple of 8 workgroups
-        const int grid = (int)std::min<int64_t>((int64_t)sc->num_cu * 5, 16384) / 8 * 8;
+        // 5 workgroups per CU, 6 with colour: every wave resident at once (about one
+        // block each at VGA), looping over its share of the list when more are
+        // listed; a multiple of 16 workgroups
+        const int64_t wgs = (int64_t)sc->num_cu * (a.clr ? 6 : 5);
+        const int grid = std::max(16, (int)std::min<int64_t>(wgs, 16384) / 16 * 16);
         HIP_TRY(launch_integrate(sc->fmt, a, grid, sc->stream));
     }
     sc->fused_frame = sc->range_on ? sc->frame : -1;

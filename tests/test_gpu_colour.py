@@ -151,3 +151,36 @@ def test_colour_calls_need_colour_enabled():
     assert c.shape[0] == sc.export(values=False)[0].shape[0]
     assert np.all(c[..., :3] == 0)          # black samples
     sc.close()
+
+
+@pytest.mark.parametrize("fmt", ["f32", "f16", "s16u8"])
+@pytest.mark.parametrize("colour", [False, True])
+@pytest.mark.parametrize("seen", ["nothing", "pixel", "tile", "holes"])
+def test_frames_that_see_little(seen, colour, fmt):
+    """Visible lists from empty to uneven, so that most waves of the integration
+    find no block of their own: the counts are the oracle's and the volume is its
+    volume in every form, with and without colour.  Bars as in the other tests;
+    half precision rounds F by 2^-11 relative at most at each of its fusions, the
+    16-bit form by half a step."""
+    st = make_stream("tiny", n_frames=4)
+    keep = np.zeros(st.depth[0].shape, bool)
+    if seen == "pixel":
+        keep[57, 91] = True
+    elif seen == "tile":
+        keep[32:64, 64:80] = True
+    elif seen == "holes":
+        keep[:, ::3] = True
+        keep[40:80, :90] = False
+    st.depth = np.where(keep, st.depth, np.array([0.0, np.nan, np.inf, -1.0], np.float32)[:, None, None])
+    print(f"case: tiny, {seen}, {fmt}, colour {colour}", flush=True)
+    g, o = fuse_both(st, 4, fmt=fmt, plain_first=0 if colour else 4)
+    tol = {"f32": 1e-5, "f16": lambda W: 2.0 ** -11 * (np.asarray(W, np.float64) + 1) + 1e-5,
+           "s16u8": lambda W: (0.5 / 32767 + 4 * 2.0 ** -23) * (np.asarray(W, np.float64) + 1) + 1e-6}[fmt]
+    if seen == "nothing":
+        assert g.stats()["n_visible_last"] == 0 and g.stats()["n_allocated"] == 0
+    else:
+        compare_volumes(g.export(), o.export(), tol=tol, cands=o.export_candidates(),
+                        g_colour=g.export_colour(), o_colour=o.export_colour())
+        so = o.stats()
+        assert g.stats()["n_visible_last"] == so["n_visible"]
+    g.close()
