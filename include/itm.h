@@ -98,7 +98,7 @@ itm_scene *itm_scene_create_ex(float voxel_size, float mu, int32_t max_w, int64_
 /* Free every device and host resource of the scene -- the hash table and the
  * voxel block array of section "Hash Table and Hashing Function" / "Voxel Block
  * Array", the visible list, the search-range bins, the tracker's, colour's,
- * refiner's and swapping's buffers, the exports' staging (synchronises its
+ * refiner's and swapping's buffers, the staging (synchronises its
  * stream).  NULL is ignored. */
 void itm_scene_destroy(itm_scene *scene);
 
@@ -188,7 +188,9 @@ itm_status itm_export_blocks(itm_scene *scene, int32_t *coords, float *sdf, floa
  *   sdf, w  HOST float[n * 512] each, export layout; F in [-1, 1], W an
  *           integer in [0, max_w]
  * ITM_ERR_ARG for NULL buffers, repeated keys or values out of range (nothing
- * is changed then).  Synchronises the stream. */
+ * is changed then).  From 48 MiB on the arrays go through the export's pinned
+ * staging, filled by at most 8 threads that end with the call.  Synchronises the
+ * stream. */
 itm_status itm_import_blocks(itm_scene *scene, const int32_t *coords, const float *sdf, const float *w,
                              int64_t n);
 

@@ -112,8 +112,8 @@ struct itm_scene {
 
     uchar4 *clr = nullptr;            // [vba_cap][512] colour voxels, allocated on enable
 
-    // export staging, two slots of kStageBytes on the device and pinned on the
-    // host, allocated at the first export
+    // staging of the exports and of large imports, two slots of kStageBytes pinned on
+    // the host and (exports) on the device, allocated at the first
     uint8_t *stage_dev = nullptr, *stage_host = nullptr;
     hipEvent_t stage_ev[2] = {nullptr, nullptr};
 
@@ -953,34 +953,126 @@ itm_status collect_blocks(itm_scene *sc, std::vector<BlockRec> &recs)
 constexpr size_t kStageBytes = size_t(16) << 20;   // a slot: 4096 blocks of F and W
 
 // one destination array: bytes per block, in block order
-struct OutPart {
-    uint8_t *dst;
+// one array of the caller's, bytes per block
+struct HostPart {
+    uint8_t *p;
     size_t bytes;
 };
 
-itm_status ensure_stage(itm_scene *sc)
+// the two pinned slots, with an event each for the copy that reads or writes it;
+// where the memory cannot be had, copies go to and from the caller's pages directly
+itm_status ensure_slots(itm_scene *sc)
 {
-    if (!sc->stage_dev)
-        if (itm_status st = dev_alloc((void **)&sc->stage_dev, 2 * kStageBytes, "export staging")) return st;
     for (hipEvent_t &e : sc->stage_ev)
         if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     if (!sc->stage_host && hipHostMalloc((void **)&sc->stage_host, 2 * kStageBytes) != hipSuccess) {
-        sc->stage_host = nullptr;   // without it the copies go to the caller's pages directly
+        sc->stage_host = nullptr;
         (void)hipGetLastError();
     }
     return ITM_OK;
 }
 
-// share t of n of a chunk's copies: m blocks from block off, the parts back to back at src
-void copy_share(const OutPart *parts, int n_parts, const uint8_t *src, int64_t off, int64_t m, int t, int n)
-{
-    for (int k = 0; k < n_parts; k++) {
-        const size_t total = parts[k].bytes * (size_t)m;
-        const size_t a = total * t / n, b = total * (t + 1) / n;
-        std::memcpy(parts[k].dst + parts[k].bytes * (size_t)off + a, src + a, b - a);
-        src += total;
+// Threads that copy chunks of blocks between the caller's arrays and the pinned
+// slots (chunk c in slot c & 1, the parts back to back), each its share of every
+// chunk.  The caller of give() and wait() is the one thread that drives them.
+class SlotCopier {
+public:
+    // out: from the slots to the arrays, else from the arrays to the slots
+    SlotCopier(uint8_t *slots, const HostPart *parts, int n_parts, int64_t n, bool out)
+        : slots_(slots), parts_(parts), n_parts_(n_parts), n_(n), out_(out)
+    {
+        for (int k = 0; k < n_parts; k++) per_ += parts[k].bytes;
+        chunk_ = (int64_t)(kStageBytes / per_);
+        chunks_ = (n + chunk_ - 1) / chunk_;
+        // one thread per 4 MiB, at most 8; where none can be started the caller copies
+        const int want = (int)std::min<size_t>({8, per_ * (size_t)n / (4 << 20),
+                                                std::max(1u, std::thread::hardware_concurrency())});
+        try {
+            pool_.reserve(8);
+            for (int t = 0; t < want; t++) pool_.emplace_back([this, t] { work(t); });
+        } catch (...) {
+        }
+        std::lock_guard<std::mutex> lk(mu_);
+        workers_ = (int)pool_.size();
     }
-}
+    ~SlotCopier()
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            stop_ = true;
+            cv_.notify_all();
+        }
+        for (std::thread &t : pool_) t.join();
+    }
+    int64_t chunks() const { return chunks_; }
+    int64_t first(int64_t c) const { return c * chunk_; }
+    int64_t size(int64_t c) const { return std::min(chunk_, n_ - c * chunk_); }
+    size_t bytes(int64_t c) const { return per_ * (size_t)size(c); }
+    uint8_t *slot(int64_t c) const { return slots_ + (c & 1) * kStageBytes; }
+    void give(int64_t c)   // chunk c may be copied now
+    {
+        if (pool_.empty()) {
+            share(c, 0, 1);
+            return;
+        }
+        std::lock_guard<std::mutex> lk(mu_);
+        left_[c & 1] = workers_;
+        ready_ = c + 1;
+        cv_.notify_all();
+    }
+    void wait(int64_t c)   // the chunk last given in chunk c's slot is copied
+    {
+        std::unique_lock<std::mutex> lk(mu_);
+        cv_.wait(lk, [&] { return left_[c & 1] == 0; });
+    }
+    void finish()          // every chunk was given: return when all are copied
+    {
+        wait(0);
+        wait(1);
+    }
+
+private:
+    void share(int64_t c, int t, int n) const
+    {
+        uint8_t *s = slot(c);
+        for (int k = 0; k < n_parts_; k++) {
+            const size_t total = parts_[k].bytes * (size_t)size(c);
+            const size_t a = total * t / n, b = total * (t + 1) / n;
+            uint8_t *p = parts_[k].p + parts_[k].bytes * (size_t)first(c);
+            if (out_) std::memcpy(p + a, s + a, b - a);
+            else std::memcpy(s + a, p + a, b - a);
+            s += total;
+        }
+    }
+    void work(int t)
+    {
+        for (int64_t c = 0; c < chunks_; c++) {
+            int n;
+            {
+                std::unique_lock<std::mutex> lk(mu_);
+                cv_.wait(lk, [&] { return ready_ > c || stop_; });
+                if (ready_ <= c) return;
+                n = workers_;
+            }
+            share(c, t, n);
+            std::lock_guard<std::mutex> lk(mu_);
+            if (--left_[c & 1] == 0) cv_.notify_all();
+        }
+    }
+    uint8_t *slots_;
+    const HostPart *parts_;
+    int n_parts_;
+    int64_t n_, chunk_ = 0, chunks_ = 0;
+    bool out_;
+    size_t per_ = 0;
+    std::mutex mu_;
+    std::condition_variable cv_;
+    int64_t ready_ = 0;      // chunks given
+    int left_[2] = {0, 0};   // per slot: threads still copying
+    int workers_ = 0;
+    bool stop_ = false;
+    std::vector<std::thread> pool_;
+};
 
 // n blocks' data to the destinations, in chunks through two slots of staging: while
 // a chunk crosses to the pinned slot, the threads copy the one before to the
@@ -990,101 +1082,90 @@ void copy_share(const OutPart *parts, int n_parts, const uint8_t *src, int64_t o
 // 128 MiB take 13 ms by one copy into them, 9.5 ms by one thread from pinned memory,
 // 2.3 ms by eight, the transfer 2.4 ms beside them.
 template <typename Fill>
-itm_status stream_out(itm_scene *sc, int64_t n, const OutPart *parts, int n_parts, Fill fill)
+itm_status stream_out(itm_scene *sc, int64_t n, const HostPart *parts, int n_parts, Fill fill)
 {
-    if (itm_status st = ensure_stage(sc)) return st;
-    size_t per = 0;
-    for (int k = 0; k < n_parts; k++) per += parts[k].bytes;
-    const int64_t chunk = (int64_t)(kStageBytes / per), chunks = (n + chunk - 1) / chunk;
-    auto size_of = [&](int64_t c) { return std::min(chunk, n - c * chunk); };
+    if (itm_status st = ensure_slots(sc)) return st;
+    if (!sc->stage_dev)
+        if (itm_status st = dev_alloc((void **)&sc->stage_dev, 2 * kStageBytes, "export staging")) return st;
     if (!sc->stage_host) {
-        for (int64_t c = 0; c < chunks; c++) {
+        size_t per = 0;
+        for (int k = 0; k < n_parts; k++) per += parts[k].bytes;
+        const int64_t chunk = (int64_t)(kStageBytes / per);
+        for (int64_t off = 0; off < n; off += chunk) {
+            const int64_t m = std::min(chunk, n - off);
             const uint8_t *src = sc->stage_dev;
-            HIP_TRY(fill(c * chunk, size_of(c), sc->stage_dev));
+            HIP_TRY(fill(off, m, sc->stage_dev));
             for (int k = 0; k < n_parts; k++) {
-                const size_t total = parts[k].bytes * (size_t)size_of(c);
-                HIP_TRY(hipMemcpyAsync(parts[k].dst + parts[k].bytes * (size_t)(c * chunk), src, total,
+                HIP_TRY(hipMemcpyAsync(parts[k].p + parts[k].bytes * (size_t)off, src, parts[k].bytes * (size_t)m,
                                        hipMemcpyDeviceToHost, sc->stream));
-                src += total;
+                src += parts[k].bytes * (size_t)m;
             }
             HIP_TRY(hipStreamSynchronize(sc->stream));
         }
         return ITM_OK;
     }
-    std::mutex mu;
-    std::condition_variable cv;
-    int64_t ready = 0;          // chunks in their pinned slots
-    int left[2] = {0, 0};       // per slot: threads still copying from it
-    bool stop = false;
-    std::vector<std::thread> pool;
-    int workers = 0;
-    auto work = [&](int t) {
-        for (int64_t c = 0; c < chunks; c++) {
-            int nw;
-            {
-                std::unique_lock<std::mutex> lk(mu);
-                cv.wait(lk, [&] { return ready > c || stop; });
-                if (stop) return;
-                nw = workers;
-            }
-            copy_share(parts, n_parts, sc->stage_host + (c & 1) * kStageBytes, c * chunk, size_of(c), t, nw);
-            std::lock_guard<std::mutex> lk(mu);
-            if (--left[c & 1] == 0) cv.notify_all();
-        }
-    };
-    // one thread per 4 MiB, at most 8; where none can be started this one copies
-    const int want = (int)std::min<size_t>({8, per * (size_t)n / (4 << 20),
-                                            std::max(1u, std::thread::hardware_concurrency())});
-    try {
-        pool.reserve(8);
-        for (int t = 0; t < want; t++) pool.emplace_back(work, t);
-    } catch (...) {
-    }
-    const int started = (int)pool.size();
-    {
-        std::lock_guard<std::mutex> lk(mu);
-        workers = started;
-    }
+    SlotCopier cp(sc->stage_host, parts, n_parts, n, true);
     hipError_t e = hipSuccess;
-    for (int64_t c = 0; c <= chunks && e == hipSuccess; c++) {
-        if (c < chunks) {   // chunk c on its way, once its slot is free again
-            const int s = c & 1;
-            {
-                std::unique_lock<std::mutex> lk(mu);
-                cv.wait(lk, [&] { return left[s] == 0; });
-            }
-            uint8_t *dev = sc->stage_dev + s * kStageBytes;
-            e = fill(c * chunk, size_of(c), dev);
+    for (int64_t c = 0; c <= cp.chunks() && e == hipSuccess; c++) {
+        if (c < cp.chunks()) {   // chunk c on its way, once its slot is free again
+            cp.wait(c);
+            uint8_t *dev = sc->stage_dev + (c & 1) * kStageBytes;
+            e = fill(cp.first(c), cp.size(c), dev);
             if (e == hipSuccess)
-                e = hipMemcpyAsync(sc->stage_host + s * kStageBytes, dev, per * (size_t)size_of(c),
-                                   hipMemcpyDeviceToHost, sc->stream);
-            if (e == hipSuccess) e = hipEventRecord(sc->stage_ev[s], sc->stream);
+                e = hipMemcpyAsync(cp.slot(c), dev, cp.bytes(c), hipMemcpyDeviceToHost, sc->stream);
+            if (e == hipSuccess) e = hipEventRecord(sc->stage_ev[c & 1], sc->stream);
         }
         if (c > 0 && e == hipSuccess) {   // chunk c - 1 has arrived: hand it out
-            const int64_t p = c - 1;
-            e = hipEventSynchronize(sc->stage_ev[p & 1]);
-            if (e != hipSuccess) break;
-            if (started == 0) {
-                copy_share(parts, n_parts, sc->stage_host + (p & 1) * kStageBytes, p * chunk, size_of(p), 0, 1);
-            } else {
-                std::lock_guard<std::mutex> lk(mu);
-                left[p & 1] = started;
-                ready = p + 1;
-                cv.notify_all();
-            }
+            e = hipEventSynchronize(sc->stage_ev[(c - 1) & 1]);
+            if (e == hipSuccess) cp.give(c - 1);
         }
     }
-    if (e != hipSuccess) {
-        std::lock_guard<std::mutex> lk(mu);
-        stop = true;
-        cv.notify_all();
-    }
-    for (std::thread &t : pool) t.join();
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(sc->stream);   // nothing writes to the staging any more
         return fail(ITM_ERR_HIP, "export failed: %s", hipGetErrorString(e));
     }
+    cp.finish();
     return ITM_OK;
+}
+
+// The way in: n blocks' data from the caller's arrays, part k of block i to dst[k] +
+// i * its bytes.  The threads fill one slot while the other crosses.  Enqueued on
+// return (the slots are still read until the stream gets there).  A runtime copy
+// from pageable memory goes through pinned pages too, but with one thread: an import
+// of 32768 blocks (128 MiB) took 4.91 ms so, now 3.66; of 16384 2.56 and 2.11, of
+// 8192 1.20 and 1.26, so below three slots' worth it is left to the runtime.
+hipError_t stream_in(itm_scene *sc, int64_t n, const HostPart *parts, int n_parts, uint8_t *const *dst)
+{
+    size_t per = 0;
+    for (int k = 0; k < n_parts; k++) per += parts[k].bytes;
+    if (per * (size_t)n < 3 * kStageBytes || ensure_slots(sc) != ITM_OK || !sc->stage_host) {
+        hipError_t e = hipSuccess;
+        for (int k = 0; k < n_parts && e == hipSuccess; k++)
+            e = hipMemcpyAsync(dst[k], parts[k].p, parts[k].bytes * (size_t)n, hipMemcpyHostToDevice, sc->stream);
+        return e;
+    }
+    SlotCopier cp(sc->stage_host, parts, n_parts, n, false);
+    hipError_t e = hipStreamSynchronize(sc->stream);   // nothing uses the slots
+    for (int64_t c = 0; c <= cp.chunks() && e == hipSuccess; c++) {
+        if (c < cp.chunks()) {   // fill chunk c's slot once chunk c - 2 has crossed
+            if (c >= 2) e = hipEventSynchronize(sc->stage_ev[c & 1]);
+            if (e != hipSuccess) break;
+            cp.give(c);
+        }
+        if (c > 0) {             // chunk c - 1 is in its slot
+            const int64_t p = c - 1;
+            cp.wait(p);
+            const uint8_t *src = cp.slot(p);
+            for (int k = 0; k < n_parts && e == hipSuccess; k++) {
+                const size_t bytes = parts[k].bytes * (size_t)cp.size(p);
+                e = hipMemcpyAsync(dst[k] + parts[k].bytes * (size_t)cp.first(p), src, bytes, hipMemcpyHostToDevice,
+                                   sc->stream);
+                src += bytes;
+            }
+            if (e == hipSuccess) e = hipEventRecord(sc->stage_ev[p & 1], sc->stream);
+        }
+    }
+    return e;
 }
 
 }  // namespace
@@ -1111,10 +1192,10 @@ itm_status itm_export_blocks(itm_scene *sc, int32_t *coords, float *sdf, float *
         return ITM_OK;
     }
     if (!sc->swap) {
-        OutPart parts[2];
+        HostPart parts[2];
         int k = 0;
-        if (sdf) parts[k++] = OutPart{(uint8_t *)sdf, sizeof(float) * kBlockVox};
-        if (w) parts[k++] = OutPart{(uint8_t *)w, sizeof(float) * kBlockVox};
+        if (sdf) parts[k++] = HostPart{(uint8_t *)sdf, sizeof(float) * kBlockVox};
+        if (w) parts[k++] = HostPart{(uint8_t *)w, sizeof(float) * kBlockVox};
         return stream_out(sc, n, parts, k, [&](int64_t off, int64_t m, uint8_t *dst) {
             float *f = (float *)dst, *wv = sdf ? f + m * kBlockVox : f;
             return launch_export_floats(sc->fmt, sc->sdf, sc->w, b.out_ent + off, m, sdf ? f : nullptr,
@@ -1316,10 +1397,10 @@ itm_status itm_import_blocks(itm_scene *sc, const int32_t *coords, const float *
     FrameGeom g = {};
     FuseArgs a = frame_args(sc, g, false);
     auto load = [&](int64_t off, int64_t m) -> hipError_t {
-        hipError_t e = hipMemcpyAsync(d_s, sdf + off * kBlockVox, blk_bytes * m, hipMemcpyHostToDevice, sc->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(d_w, w + off * kBlockVox, blk_bytes * m, hipMemcpyHostToDevice, sc->stream);
-        return e;
+        const HostPart parts[2] = {{(uint8_t *)(sdf + off * kBlockVox), blk_bytes},
+                                   {(uint8_t *)(w + off * kBlockVox), blk_bytes}};
+        uint8_t *const dst[2] = {(uint8_t *)d_s, (uint8_t *)d_w};
+        return stream_in(sc, m, parts, 2, dst);
     };
     hipError_t e = hipSuccess;
     if (n > 0) {
@@ -1377,7 +1458,7 @@ itm_status itm_export_colour(itm_scene *sc, uint8_t *rgbw, int64_t capacity, int
     DevMem mem;
     SortedBlocks b;
     if (itm_status st = sorted_blocks(sc, n, mem, &b)) return st;
-    const OutPart part{rgbw, sizeof(uchar4) * kBlockVox};
+    const HostPart part{rgbw, sizeof(uchar4) * kBlockVox};
     return stream_out(sc, n, &part, 1, [&](int64_t off, int64_t m, uint8_t *dst) {
         return launch_export_colour(sc->clr, b.out_ent + off, m, (uchar4 *)dst, sc->stream);
     });

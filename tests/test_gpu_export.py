@@ -44,6 +44,20 @@ def test_round_trip_in_key_order(n, fmt):
     assert np.array_equal(gF, want[at])
 
 
+@pytest.mark.parametrize("n", [12287, 12288, 20481])
+def test_imports_through_the_staging(n):
+    # 12288 blocks are the first to go through the pinned slots (4096 blocks each)
+    itm, torch = gpu()
+    c, F, W = _map(n, n)
+    at = np.lexsort((c[:, 2], c[:, 1], c[:, 0]))
+    with _scene(itm, n, "f32") as sc:
+        for k in range(2):     # the second import changes every block
+            sc.import_blocks(c, F * np.float32(1 - k / 2), W)
+        gc, gF, gW = sc.export()
+    assert np.array_equal(gc, c[at]) and np.array_equal(gW, W[at])
+    assert np.array_equal(gF, F[at] * np.float32(0.5))
+
+
 def test_partial_outputs_and_colour():
     itm, torch = gpu()
     n = 5000
