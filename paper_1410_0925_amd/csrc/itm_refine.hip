@@ -69,6 +69,7 @@ constexpr int kGrid = 2 * kHalf + kPlane;
 // K steps 0 .. 13 of a layer with 16 input channels, as a lane holds them: K step p
 // is taps 2 p (lanes 0-31) and 2 p + 1 (lanes 32-63), channels 8 h .. 8 h + 7 with h =
 // (lane >> 4) & 1; tap 27 is zero.  W: bf16 [tap][row][channel].
+template <int P0 = 0, int P1 = 14>
 __device__ __forceinline__ void load_weights(const uint16_t *W, bool flip, int lane, i32x4 (&w)[14])
 {
     const int n = lane & 15, h = (lane >> 4) & 1, s = lane >> 5;
@@ -77,9 +78,19 @@ __device__ __forceinline__ void load_weights(const uint16_t *W, bool flip, int l
     asm volatile("" : "+v"(at));
     const int step = flip ? -kC * kC : kC * kC;
 #pragma unroll
-    for (int p = 0; p < 14; p++)
+    for (int p = P0; p < P1; p++)
         w[p] = *reinterpret_cast<const i32x4 *>(&W[at + (p < 13 ? 2 * p + s : 26) * step]);
-    if (s) w[13] = i32x4{0, 0, 0, 0};
+    if (P1 == 14 && s) w[13] = i32x4{0, 0, 0, 0};
+}
+
+// the next convolution's weights, into the registers that the products of plane r of
+// this one read last
+template <int NZ>
+__device__ __forceinline__ void next_weights(int r, const uint16_t *W, bool flip, int lane, i32x4 (&w)[14])
+{
+    if (r == NZ - 1) load_weights<0, 4>(W, flip, lane, w);
+    if (r == NZ) load_weights<4, 9>(W, flip, lane, w);
+    if (r == NZ + 1) load_weights<9, 14>(W, flip, lane, w);
 }
 
 // acc[j] (lane: voxel column lane & 15, channels 4 (lane >> 4) + r) = the
@@ -91,9 +102,15 @@ __device__ __forceinline__ void load_weights(const uint16_t *W, bool flip, int l
 //   S  in-plane tap 8 of the plane before with tap 0 of this one: taps 8, 9 of
 //      plane r - 1; its first half, alone, is tap 26 of plane r - 3;
 //   O  in-plane pairs (1,2) (3,4) (5,6) (7,8): dz = 1 of plane r - 1.
-template <int NZ>
-__device__ __forceinline__ void conv16(const uint16_t *grid, const i32x4 (&w)[14], int yp, int z0, int lane,
-                                       f32x4 (&acc)[NZ])
+//
+// In training (NZ = 4, two waves per SIMD) the reads run a plane ahead of the
+// products: issued as they were used, two at a time, each convolution took twice
+// what its reads take, and a training step 458 us per 8 (now 424).  Inference (NZ =
+// 8, three waves per SIMD) has neither the registers for it (68 spilled) nor the
+// need.  after(r) runs behind the products of plane r.
+template <int NZ, typename After>
+__device__ __forceinline__ void conv16(const uint16_t *grid, i32x4 (&w)[14], int yp, int z0, int lane,
+                                       f32x4 (&acc)[NZ], After after)
 {
     const int n = lane & 15, h = (lane >> 4) & 1, s = lane >> 5;
     // in-plane tap 0 of input plane r = 0; the second half of the lanes reads the
@@ -103,26 +120,42 @@ __device__ __forceinline__ void conv16(const uint16_t *grid, const i32x4 (&w)[14
     const i32x4 zero = {0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < NZ; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    i32x4 S = zero;
+    // f[a]: the pair from in-plane tap a of plane r (even: E, odd: O, 8: S)
+    auto load = [&](int r, i32x4 (&f)[9]) {
+        const bool edge = NZ == 8 && (r == 0 || r == NZ + 1);   // the halo plane: zeros
+#pragma unroll
+        for (int q = 0; q < 9; q++) {
+            if (q < 8 && (q & 1) && !(r >= 1 && r <= NZ)) continue;
+            if (q < 8 && !(q & 1) && edge) {
+                f[q] = zero;
+                continue;
+            }
+            const uint16_t *b = q == 8 ? b78 : q == 2 || q == 5 ? b8 : b1;
+            f[q] = *reinterpret_cast<const i32x4 *>(b + (r * 100 + q % 3 + 10 * (q / 3)) * 8);
+        }
+    };
+    constexpr bool kAhead = NZ == 4;
+    i32x4 f[2][9], S = zero;
+    if (kAhead) load(0, f[0]);
 #pragma unroll
     for (int r = 0; r < NZ + 2; r++) {
-        const bool edge = NZ == 8 && (r == 0 || r == NZ + 1);   // the halo plane: zeros
-        auto at = [&](const uint16_t *b, int a) -> i32x4 {      // the pair from in-plane tap a of plane r
-            return *reinterpret_cast<const i32x4 *>(b + (r * 100 + a % 3 + 10 * (a / 3)) * 8);
-        };
+        if (!kAhead) load(r, f[r & 1]);
+        else if (r < NZ + 1) load(r + 1, f[(r + 1) & 1]);
+        if (kAhead) __builtin_amdgcn_sched_barrier(0);
+        const i32x4 (&c)[9] = f[r & 1];
         if (r >= 1 && r <= NZ) {
             acc[r - 1] = mfma32(w[4], S, acc[r - 1]);
 #pragma unroll
-            for (int q = 0; q < 4; q++) acc[r - 1] = mfma32(w[5 + q], at(q == 2 ? b8 : b1, 2 * q + 1), acc[r - 1]);
+            for (int q = 0; q < 4; q++) acc[r - 1] = mfma32(w[5 + q], c[2 * q + 1], acc[r - 1]);
         }
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            const i32x4 E = edge ? zero : at(q == 1 ? b8 : b1, 2 * q);
-            if (r < NZ) acc[r] = mfma32(w[q], E, acc[r]);
-            if (r >= 2) acc[r - 2] = mfma32(w[9 + q], E, acc[r - 2]);
+            if (r < NZ) acc[r] = mfma32(w[q], c[2 * q], acc[r]);
+            if (r >= 2) acc[r - 2] = mfma32(w[9 + q], c[2 * q], acc[r - 2]);
         }
-        S = at(b78, 8);
+        S = c[8];
         if (r >= 2) acc[r - 2] = mfma32(w[13], s ? zero : S, acc[r - 2]);
+        after(r);
     }
 }
 
@@ -234,7 +267,7 @@ __device__ __forceinline__ void infer_layers(InferLds &L, const RefineParams &P,
         for (int j = 0; j < 8; j++)
             *reinterpret_cast<uint2 *>(&L.grid[out + j * kPlane]) = pack4(relu(acc[j], b));
         __syncthreads();
-        conv16<8>(L.grid, w, wave, 0, lane, acc);
+        conv16<8>(L.grid, w, wave, 0, lane, acc, [](int) {});
     }
     const float b = P.bias[3 * kC];
 #pragma unroll
@@ -271,9 +304,9 @@ __global__ __launch_bounds__(kInferThreads) __attribute__((amdgpu_waves_per_eu(3
 // lanes with consecutive channels fall in different LDS banks), beside the grid the
 // convolutions read, which holds the back-propagated gradient afterwards (142 KB:
 // one workgroup per CU).  A batch of 256 blocks is one block per CU, so the time is
-// one block's chain of layers: 44 us, 14 of them the weight gradients and 20 the six
-// convolutions at their LDS rate (68 us with 16 waves of 2 tiles, activations
-// copied to channel rows layer by layer).
+// one block's chain of layers, bound by its LDS reads (14 us at their rate) and the
+// waits between them: 37.5 us (68 with 16 waves of 2 tiles and activations copied to
+// channel rows layer by layer, 43 with nothing read ahead).
 constexpr int kTrainWaves = 8, kTrainNZ = 4;
 constexpr int kRowT = 512 + 8;
 constexpr int kRowA = 100 * 8 + 8;
@@ -322,10 +355,12 @@ __device__ __forceinline__ i32x4 window8(i32x4 r0, i32x4 r1, int d)
 // Weight gradient of the taps (dx, dy, dz), D0 <= dx < D1, of a layer: per tap a 16 x
 // 16 GEMM (M = output channel, N = input channel) over the 512 voxels, K = 32 voxels
 // (4 x-rows) a step, lane group kq taking row 4 ks + kq.  A = 8 voxels of the
-// gradient's channel row, held in registers for all taps (g); B = the input row at
-// the tap's (y, z) offset, read once for its three x offsets.
+// gradient's channel row; B = the input row at the tap's (y, z) offset, read once
+// for its three x offsets.  Both are read four K steps ahead of the products: with the
+// gradient's rows held in registers for all taps instead, there was no room for that
+// (54 registers spilled, 465 us per 8 steps against 413, and 424 without reading ahead).
 template <int D0, int D1, bool FIRST>
-__device__ __forceinline__ void weight_grad(const uint16_t *xT, const i32x4 (&g)[16], int c, int lane, float *gp)
+__device__ __forceinline__ void weight_grad(const uint16_t *xT, const uint16_t *gT, int c, int lane, float *gp)
 {
     const int kq = lane >> 4, n = lane & 15, dz = c / 3, dy = c % 3;
     // row 4 ks + kq is y = 4 (ks & 1) + kq, z = ks >> 1
@@ -334,18 +369,35 @@ __device__ __forceinline__ void weight_grad(const uint16_t *xT, const i32x4 (&g)
     f32x4 acc[3];
 #pragma unroll
     for (int d = D0; d < D1; d++) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // four rows ahead of the four in use
+    const uint16_t *gr = &gT[n * kRowT + 8 * kq];
+    i32x4 x[2][4][FIRST ? 2 : 1], g[2][4];
+    auto load = [&](int b) {
 #pragma unroll
-    for (int ks = 0; ks < 16; ks++) {
-        const uint16_t *p = base + ((ks >> 1) * 10 + 4 * (ks & 1)) * (FIRST ? 16 : 8);
-        i32x4 r0 = *reinterpret_cast<const i32x4 *>(p), r1 = {0, 0, 0, 0};
-        if (FIRST) {   // layer 1's input is the 10^3 grid: elements dx .. dx + 7 of its row
-            r1 = *reinterpret_cast<const i32x4 *>(p + 8);
-            if (n > 1) r0 = r1 = i32x4{0, 0, 0, 0};
+        for (int q = 0; q < 4; q++) {
+            const int ks = 4 * b + q;
+            const uint16_t *p = base + ((ks >> 1) * 10 + 4 * (ks & 1)) * (FIRST ? 16 : 8);
+            i32x4 (&r)[FIRST ? 2 : 1] = x[b & 1][q];
+            r[0] = *reinterpret_cast<const i32x4 *>(p);
+            g[b & 1][q] = *reinterpret_cast<const i32x4 *>(gr + 32 * ks);
+            if constexpr (FIRST) {   // layer 1's input is the 10^3 grid: elements dx .. dx + 7 of its row
+                r[1] = *reinterpret_cast<const i32x4 *>(p + 8);
+                if (n > 1) r[0] = r[1] = i32x4{0, 0, 0, 0};
+            }
         }
-        if ((ks & 3) == 0) __builtin_amdgcn_sched_barrier(0);   // 4 rows in flight, not all 16
+    };
+    load(0);
 #pragma unroll
-        for (int d = D0; d < D1; d++)
-            acc[d] = mfma32(g[ks], FIRST ? window8(r0, r1, d) : shift_row(r0, d - 1), acc[d]);
+    for (int b = 0; b < 4; b++) {
+        if (b < 3) load(b + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int d = D0; d < D1; d++) {
+                const i32x4 (&r)[FIRST ? 2 : 1] = x[b & 1][q];
+                acc[d] = mfma32(g[b & 1][q], FIRST ? window8(r[0], r[FIRST ? 1 : 0], d) : shift_row(r[0], d - 1), acc[d]);
+            }
     }
 #pragma unroll
     for (int d = D0; d < D1; d++)
@@ -358,14 +410,10 @@ __device__ __forceinline__ void weight_grad(const uint16_t *xT, const i32x4 (&g)
 template <bool FIRST>
 __device__ __forceinline__ void weight_grads(const uint16_t *xT, const uint16_t *gT, int wave, int lane, float *gp)
 {
-    i32x4 g[16];
-#pragma unroll
-    for (int ks = 0; ks < 16; ks++)
-        g[ks] = *reinterpret_cast<const i32x4 *>(&gT[(lane & 15) * kRowT + 8 * (4 * ks + (lane >> 4))]);
-    weight_grad<0, 3, FIRST>(xT, g, wave, lane, gp);
-    if (wave == 1) weight_grad<0, 1, FIRST>(xT, g, 8, lane, gp);
-    else if (wave == 2) weight_grad<1, 2, FIRST>(xT, g, 8, lane, gp);
-    else if (wave == 3) weight_grad<2, 3, FIRST>(xT, g, 8, lane, gp);
+    weight_grad<0, 3, FIRST>(xT, gT, wave, lane, gp);
+    if (wave == 1) weight_grad<0, 1, FIRST>(xT, gT, 8, lane, gp);
+    else if (wave == 2) weight_grad<1, 2, FIRST>(xT, gT, 8, lane, gp);
+    else if (wave == 3) weight_grad<2, 3, FIRST>(xT, gT, 8, lane, gp);
 }
 
 __global__ __launch_bounds__(kTrainWaves * 64) void k_refine_train(RefineArgs a)
@@ -438,13 +486,10 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_refine_train(RefineArgs a)
                 }
             }
             on |= (uint64_t)bits << (16 * l);
-            i32x4 wn[14];   // the next convolution's weights travel while this one runs
-            load_weights(l < 2 ? a.P.Wf + (size_t)(l + 2) * kTaps * kC * kC : a.P.Wt + (size_t)3 * kTaps * kC * kC,
-                         l == 2, lane, wn);
+            const uint16_t *wn =
+                l < 2 ? a.P.Wf + (size_t)(l + 2) * kTaps * kC * kC : a.P.Wt + (size_t)3 * kTaps * kC * kC;
             __syncthreads();
-            conv16<NZ>(L.grid, w, yp, z0, lane, acc);
-#pragma unroll
-            for (int p = 0; p < 14; p++) w[p] = wn[p];
+            conv16<NZ>(L.grid, w, yp, z0, lane, acc, [&](int r) { next_weights<NZ>(r, wn, l == 2, lane, w); });
         }
         // residual, clamp, loss and its gradient (lanes 0-15 hold the output channel);
         // the gradient of the 15 unused channels is zero
@@ -499,13 +544,13 @@ __global__ __launch_bounds__(kTrainWaves * 64) void k_refine_train(RefineArgs a)
             __syncthreads();
             if (l > 0) {
                 // data gradient into the layer before, masked by its ReLU
-                conv16<NZ>(L.grid, w, yp, z0, lane, acc);
+                const uint16_t *wn = a.P.Wt + (size_t)(l - 1) * kTaps * kC * kC;   // (at l = 1 not used)
+                conv16<NZ>(L.grid, w, yp, z0, lane, acc, [&](int r) { next_weights<NZ>(r, wn, true, lane, w); });
                 const uint32_t m = (uint32_t)(on >> (16 * (l - 1)));
 #pragma unroll
                 for (int j = 0; j < NZ; j++)
 #pragma unroll
                     for (int r = 0; r < 4; r++) G[j][r] = (m >> (4 * j + r)) & 1u ? acc[j][r] : 0.0f;
-                if (l > 1) load_weights(a.P.Wt + (size_t)(l - 1) * kTaps * kC * kC, true, lane, w);
                 weight_grads<false>(L.aT[l - 1], L.gT, wave, lane, gp + l * kTaps * kC * kC);
             } else {
                 weight_grads<true>(L.x0T, L.gT, wave, lane, gp);
