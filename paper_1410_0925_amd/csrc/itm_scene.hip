@@ -629,9 +629,11 @@ itm_status grow_host_copies(itm_scene *sc, int64_t n_slots)
         sc->host_chunks.push_back(p);
     }
     const size_t got = sc->host_chunks.size();
-    if (got > had)   // from the vector's memory, complete on return
-        HIP_TRY(hipMemcpy(sc->chunk_tab + had, sc->host_chunks.data() + had, sizeof(uint8_t *) * (got - had),
-                          hipMemcpyHostToDevice));
+    if (got > had) {   // complete on return: a later growth may move the vector
+        HIP_TRY(hipMemcpyAsync(sc->chunk_tab + had, sc->host_chunks.data() + had, sizeof(uint8_t *) * (got - had),
+                               hipMemcpyHostToDevice, sc->stream));
+        HIP_TRY(hipStreamSynchronize(sc->stream));
+    }
     return got < want ? fail(ITM_ERR_OOM, "pinned host copies of %lld blocks", (long long)n_slots) : ITM_OK;
 }
 
@@ -1319,6 +1321,7 @@ itm_status itm_scene_enable_swapping(itm_scene *sc, int64_t device_blocks, int32
     if (e == hipSuccess) e = hipMemsetAsync(sc->swap_cnt, 0, sizeof(SwapCnt) * 2, sc->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(sc->stream);
     if (e != hipSuccess) return fail(ITM_ERR_HIP, "swapping set-up failed: %s", hipGetErrorString(e));
+    sc->host_chunks.reserve((size_t)(sc->n_entries / kSwapChunk + 1));   // no allocation in a frame but the copies'
     sc->swap_in_cap = swap_in;
     sc->swap_out_cap = swap_out;
     sc->swap = true;
