@@ -288,6 +288,7 @@ struct alignas(16) RangeRect {
 static_assert(sizeof(RangeRect) == 16, "range rectangle is 16 bytes");
 constexpr int kTile = 16;
 
+constexpr int64_t kMaxOrdered = 1 << 16;   // tiles that one workgroup puts in order
 struct RangeBins {
     int32_t *cnt;         // [n_tiles] rectangles appended (may exceed cap)
     RangeRect *rect;      // [n_tiles][cap]
@@ -295,6 +296,7 @@ struct RangeBins {
     int32_t tw, th;       // tiles per row, per column
     int32_t *unbinned;    // non-null for bins the allocation fills: set when a block went
                           // unbinned, and every tile then takes the exact path
+    int32_t *order;       // [n_tiles] the tiles, fullest bins first, or nullptr (itm_integrate.hip)
 };
 
 // the per-frame kernels: allocation and visible list (and the expected-depth

@@ -239,12 +239,21 @@ __device__ __forceinline__ void gradient(const float Fc[8], const float Ex[2][4]
     }
 }
 
-template <int FMT, bool CLR, bool REF>
+// ORD: workgroup i takes tile order[i] (the fullest bins first), else XCD-contiguous bands
+template <int FMT, bool CLR, bool REF, bool ORD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_raycast(RaycastArgs a)
 {
     const FrameGeom &g = a.fg;
     int tx, ty;
-    if (!xcd_tile((g.W + 15) / 16, (g.H + 15) / 16, tx, ty)) return;  // whole workgroup
+    if constexpr (ORD) {
+        if ((int)blockIdx.x >= a.rb.tw * a.rb.th) return;   // whole workgroup
+        const int tile = __builtin_amdgcn_readfirstlane(
+            min((uint32_t)a.rb.order[blockIdx.x], (uint32_t)(a.rb.tw * a.rb.th - 1)));
+        tx = tile % a.rb.tw;
+        ty = tile / a.rb.tw;
+    } else {
+        if (!xcd_tile((g.W + 15) / 16, (g.H + 15) / 16, tx, ty)) return;
+    }
     // the tile's expected-depth bin, loaded while the macro filter is staged
     TileBin bin;
     if (a.rb.cnt) bin = tile_bin(a.rb, tx, ty);
@@ -458,29 +467,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     if (CLR) a.rgb_out[pix] = C;
 }
 
-template <int FMT>
+template <int FMT, bool ORD>
 void launch_fmt(const RaycastArgs &a, bool clr, bool ref, int grid, hipStream_t st)
 {
     if (ref) {
-        if (clr) launch_k(k_raycast<FMT, true, true>, grid, 256, st, a);
-        else launch_k(k_raycast<FMT, false, true>, grid, 256, st, a);
+        if (clr) launch_k(k_raycast<FMT, true, true, ORD>, grid, 256, st, a);
+        else launch_k(k_raycast<FMT, false, true, ORD>, grid, 256, st, a);
     } else {
-        if (clr) launch_k(k_raycast<FMT, true, false>, grid, 256, st, a);
-        else launch_k(k_raycast<FMT, false, false>, grid, 256, st, a);
+        if (clr) launch_k(k_raycast<FMT, true, false, ORD>, grid, 256, st, a);
+        else launch_k(k_raycast<FMT, false, false, ORD>, grid, 256, st, a);
     }
 }
 
 hipError_t launch_raycast(int fmt, const RaycastArgs &a, hipStream_t st)
 {
     const int grid = xcd_grid(((a.fg.W + 15) / 16) * ((a.fg.H + 15) / 16));
-    // the colour variant and the one that reads refined blocks are kernels of
-    // their own: the plain depth raycast carries neither
+    // the colour variant, the one that reads refined blocks and the one that takes its
+    // tiles in order are kernels of their own: the plain depth raycast carries none
     const bool clr = a.clr && a.rgb_out;
     const bool ref = a.refined != nullptr;
+    const bool ord = a.rb.order != nullptr;   // (null without bins)
     switch (fmt) {
-    case ITM_VOX_F32: launch_fmt<ITM_VOX_F32>(a, clr, ref, grid, st); break;
-    case ITM_VOX_F16: launch_fmt<ITM_VOX_F16>(a, clr, ref, grid, st); break;
-    default: launch_fmt<ITM_VOX_S16U8>(a, clr, ref, grid, st); break;
+    case ITM_VOX_F32: (ord ? launch_fmt<ITM_VOX_F32, true> : launch_fmt<ITM_VOX_F32, false>)(a, clr, ref, grid, st); break;
+    case ITM_VOX_F16: (ord ? launch_fmt<ITM_VOX_F16, true> : launch_fmt<ITM_VOX_F16, false>)(a, clr, ref, grid, st); break;
+    default: (ord ? launch_fmt<ITM_VOX_S16U8, true> : launch_fmt<ITM_VOX_S16U8, false>)(a, clr, ref, grid, st); break;
     }
     return hipGetLastError();
 }

@@ -97,7 +97,7 @@ struct itm_scene {
     // integration at its pose) and 2 (filled for a raycast at another pose)
     bool range_on = false;
     int32_t range_cap = 512;
-    int32_t *bin_cnt = nullptr;       // [3][bin_tiles]
+    int32_t *bin_cnt = nullptr;       // [3][bin_tiles], then the tile orders, [2][bin_tiles]
     RangeRect *bin_rect = nullptr;    // [3][bin_tiles][range_cap]
     int64_t bin_tiles = 0;
     int32_t fused_frame = -1;         // frame whose own-pose bins are valid, -1 none
@@ -309,7 +309,7 @@ itm_status ensure_bins(itm_scene *sc, int W, int H)
     sc->bin_rect = nullptr;
     sc->bin_tiles = 0;
     sc->fused_frame = -1;
-    if (itm_status st = dev_alloc((void **)&sc->bin_cnt, sizeof(int32_t) * 3 * tiles, "range bin counts")) return st;
+    if (itm_status st = dev_alloc((void **)&sc->bin_cnt, sizeof(int32_t) * 5 * tiles, "range bin counts")) return st;
     if (itm_status st = dev_alloc((void **)&sc->bin_rect, sizeof(RangeRect) * 3 * tiles * sc->range_cap,
                                   "range bins"))
         return st;
@@ -327,6 +327,10 @@ RangeBins bin_set(const itm_scene *sc, int set, int W, int H)
     rb.tw = (W + kTile - 1) / kTile;
     rb.th = (H + kTile - 1) / kTile;
     rb.unbinned = set < 2 ? &sc->cnt->unbinned[set][0] : nullptr;   // set 2 is re-binned whole
+    const int64_t tiles = (int64_t)rb.tw * rb.th;
+    rb.order = set < 2 && tiles >= 3 * (int64_t)sc->num_cu && tiles <= kMaxOrdered
+                   ? sc->bin_cnt + (3 + set) * sc->bin_tiles
+                   : nullptr;
     return rb;
 }
 

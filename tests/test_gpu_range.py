@@ -152,3 +152,34 @@ def test_blocks_listed_when_the_workgroup_set_is_full():
     got, want = _ranges(g, o, st, st.T_wc[0])
     assert _same(got, want), f"{np.count_nonzero(got != want)} values differ"
     g.close()
+
+
+@pytest.mark.parametrize("fmt", ["f32", "f16"])
+@pytest.mark.parametrize("size", [(512, 384), (641, 353), (1281, 721)])
+def test_tiles_in_any_order(size, fmt):
+    """From 768 tiles on a raycast at the frame's own pose takes its tiles in the order
+    that the integration left (here the fewest, a ragged image, and more than the
+    order's workgroup reads at once); at the same pose with a zero of the other sign it
+    bins anew and takes them in bands.  The same rays either way: equal bit for bit."""
+    import synth
+    itm, torch = gpu()
+    W, H = size
+    K = (0.8 * W, 0.8 * W, (W - 1) / 2, (H - 1) / 2)
+    T = synth.pose_look_at([1.5, 1.2, 1.8], [0.2, 0.2, 0.2], [0, 1, 0])
+    print(f"case: corner {W}x{H}, {fmt}", flush=True)
+    sc = itm.Scene(0.02, 0.08, 100, 1 << 15, 1 << 13, fmt=fmt)
+    sc.set_search_range(True)
+    for k in range(3):
+        Tk = T.copy()
+        Tk[:3, 3] += 0.01 * k
+        depth = synth.render_plane_maps([[1, 0, 0, 0], [0, 1, 0, 0], [0, 0, 1, 0]], K, W, H, Tk)[0]
+        sc.integrate(torch.from_numpy(depth.astype(np.float32)).cuda(), K + (W, H), Tk)
+        P, N = (x.clone() for x in sc.raycast(K + (W, H), Tk))
+        other = Tk.copy()
+        assert other[3, 0] == 0.0
+        other[3, 0] = -0.0 if not np.signbit(other[3, 0]) else 0.0
+        Q, M = sc.raycast(K + (W, H), other)
+        assert (P[..., 3] > 0).float().mean() > 0.3
+        assert torch.equal(P.view(torch.int32), Q.view(torch.int32))
+        assert torch.equal(N.view(torch.int32), M.view(torch.int32))
+    sc.close()
