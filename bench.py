@@ -41,9 +41,9 @@ VOX_BYTES = {"f32": 8, "f16": 4, "s16u8": 3}
 # another frame range, reports traffic null.
 FETCH_SCALE, WRITE_SCALE = 262144.0 / 131087.7, 262144.0 / 262144.0
 TRAFFIC_KIB = {
-    ("alloc", "f32", "vga", "10..299"): {"fetch": 1064.1, "write": 1022.1, "src": "ee2915b8c96aacbf"},
-    ("integrate", "f32", "vga", "10..299"): {"fetch": 9985.7, "write": 14769.5, "src": "ee2915b8c96aacbf"},
-    ("raycast", "f32", "vga", "10..299"): {"fetch": 7426.9, "write": 9600.0, "src": "afa3ce252e9aa73b"},
+    ("alloc", "f32", "vga", "10..299"): {"fetch": 1064.7, "write": 1020.6, "src": "7284a72713b31fec"},
+    ("integrate", "f32", "vga", "10..299"): {"fetch": 9988.8, "write": 14773.9, "src": "7284a72713b31fec"},
+    ("raycast", "f32", "vga", "10..299"): {"fetch": 11698.7, "write": 9600.0, "src": "079e19b4e6ef148a"},
 }
 
 
