@@ -730,7 +730,7 @@ struct RangeLds {
     union {
         uint4 rect[256];   // per rectangle: first corner (u | v << 16), extent (likewise), z0, z1
         struct {
-            uint32_t zlo[256], zhi[256];   // binary32 bits (all values >= 0: integer order = float order)
+            uint32_t zlo[256], zhi[256];   // binary32 bits (of values >= 0: integer order = float order)
         } px;
     };
     int pre[kListSegs + 1];
@@ -805,7 +805,8 @@ __device__ __forceinline__ void tile_range(const FrameGeom &g, const VisList &li
         return;
     }
     // overflow: every visible block, rectangles clipped to the tile, min / max
-    // by LDS atomics (threads stride over the list)
+    // by LDS atomics (threads stride over the list).  z0 is never below 0; z1 is where
+    // the whole block lies behind the camera, and then adds nothing to a far end of 0
     __syncthreads();
     L.px.zlo[threadIdx.x] = __float_as_uint(INFINITY);
     L.px.zhi[threadIdx.x] = 0u;
@@ -825,11 +826,12 @@ __device__ __forceinline__ void tile_range(const FrameGeom &g, const VisList &li
             if (!block_rect(g, kx, ky, kz, r)) continue;
             const int a0 = max((int)r.u0, ux0), a1 = min((int)r.u1, ux0 + kTile - 1);
             const int b0 = max((int)r.v0, vy0), b1 = min((int)r.v1, vy0 + kTile - 1);
+            const uint32_t z0 = __float_as_uint(r.z0), z1 = r.z1 > 0.0f ? __float_as_uint(r.z1) : 0u;
             for (int y = b0; y <= b1; y++)
                 for (int x = a0; x <= a1; x++) {
                     const int p = (y - vy0) * kTile + (x - ux0);
-                    atomicMin(&L.px.zlo[p], __float_as_uint(r.z0));
-                    atomicMax(&L.px.zhi[p], __float_as_uint(r.z1));
+                    atomicMin(&L.px.zlo[p], z0);
+                    atomicMax(&L.px.zhi[p], z1);
                 }
         }
     }

@@ -183,3 +183,31 @@ def test_tiles_in_any_order(size, fmt):
         assert torch.equal(P.view(torch.int32), Q.view(torch.int32))
         assert torch.equal(N.view(torch.int32), M.view(torch.int32))
     sc.close()
+
+
+@pytest.mark.parametrize("cap", [1, 512])
+def test_blocks_behind_the_camera(cap):
+    """Listed blocks wholly behind the camera cover the image from depth 0 to 0: they
+    must not lower the far end that the blocks in front give, whether their rectangles
+    are binned (room for 512) or every tile overflows (room for 1).  Poses inside the
+    scene, turned about, and turned about outside it (every block behind); the range
+    image bit for bit, and the raycast inside it."""
+    st = make_stream("tiny", n_frames=4)
+    print(f"case: tiny, blocks behind the camera, tile capacity {cap}", flush=True)
+    g, _, _ = fuse_gpu(st, search_range=True, tile_capacity=cap)
+    o, _, _ = fuse_oracle(st, frames=4)
+    z = o.raycast(st.width, st.height, st.intrinsics, st.T_wc[3])[2]
+    about = np.diag([-1.0, 1.0, -1.0, 1.0])
+
+    def into(q):      # forward until that share of the pixels' surface is left behind
+        T = np.eye(4)
+        T[2, 3] = float(np.quantile(z[z > 0], q))
+        return st.T_wc[3] @ T
+    for what, T in (("inside", into(0.2)), ("inside, about", into(0.3) @ about), ("about", st.T_wc[3] @ about)):
+        got, want = _ranges(g, o, st, T)
+        assert (want[..., 0] == 0).all()               # some block is behind, or at the camera plane
+        assert _same(got, want), f"{what}: {np.count_nonzero(got != want)} values differ"
+        p, n = g.raycast(K_of(st), T)
+        print(compare_raycast((p.cpu().numpy(), n.cpu().numpy()),
+                              o.raycast(st.width, st.height, st.intrinsics, T, zrange=want), T))
+    g.close()
