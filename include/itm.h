@@ -340,12 +340,14 @@ itm_status itm_track_noalloc(itm_scene *scene, const float *depth, const itm_int
 /*    secondary integration F = (W_d F_d + W_h F_h) / (W_d + W_h), W = min(W_d */
 /*    + W_h, max_w);                                                          */
 /*  - swap out: of the device blocks not visible in the frame with nothing to */
-/*    merge, the first swap_out in key order move to the host (a host voxel   */
-/*    block per hash entry, kept by the library) and free their device block.  */
+/*    merge any more, the first swap_out in key order move to the host (a host */
+/*    voxel block per hash entry, kept by the library) and free their device   */
+/*    block.                                                                   */
 /* The host copies are in pinned memory (8 MiB or less at a time as they come  */
 /* to be needed, kept until the scene is destroyed; ITM_ERR_OOM, with the frame */
 /* fused and nothing moved, when there is no more), which the device reads and */
-/* writes directly; each frame synchronises the stream twice.                  */
+/* writes directly; each frame synchronises the stream twice, a third time    */
+/* where what merges decides what may leave.                                  */
 /* The raycast sees the blocks on the device only; itm_export_blocks returns    */
 /* every block wherever it is (merged when both copies exist).  Call before   */
 /* the first frame; not with colour, a refiner or itm_import_blocks            */

@@ -411,7 +411,7 @@ hipError_t launch_range_image(const FrameGeom &g, const VisList &list, const Ran
 struct alignas(16) SwapRec {
     unsigned long long key;
     int32_t e;
-    int32_t pad;
+    int32_t pend;        // not visible, its host copy not merged: leaves if it merges now
 };
 constexpr int kSwapPasses = 4;             // of the choice: 12 bits of the 48-bit key each
 constexpr int kSwapHistWords = 2 * kSwapPasses << 12;
@@ -420,7 +420,11 @@ constexpr int kSwapMoveWgs = 128;
 constexpr int kSwapChunk = 2048;           // host copies per allocation
 struct SwapCnt {
     unsigned long long cand;   // candidates: swap in | swap out << 32
-    uint32_t chosen[2];        // places drawn in the lists of the chosen
+    uint32_t pend;             // of the outs, those that are ins too (SwapRec::pend)
+    uint32_t pend_in;          // of those, chosen to merge in this frame
+    uint32_t in;               // places drawn in the list of the ins, and in those of the
+    uint32_t pad;              // outs: at once | after their merge << 24 | workgroups
+    unsigned long long out;    // done << 48 (a transfer is at most 2^20 blocks)
 };
 struct SwapSel {               // of the cap-th smallest key: its digits so far, and its
     unsigned long long prefix; // place (from 1) among the keys that share them
@@ -443,8 +447,9 @@ struct SwapSelArgs {
     SwapCnt *cnt, *cnt_next;  // this frame's, and the next one's (zeroed here)
     uint32_t *hist;           // digit counts: [list][pass][4096]
     SwapSel *sel;             // [list][pass]
-    int32_t *chosen[2];       // entries: in, out
-    int32_t *moves;           // [2], host memory: how many of each
+    int32_t *chosen[3];       // entries: in, out, out after their merge
+    int32_t *moves;           // [3], host memory: how many of each; outs -1: not
+                              // chosen yet (launch_swap_choose)
 };
 struct SwapMoveArgs {
     HashView h;
@@ -462,7 +467,8 @@ struct SwapMoveArgs {
     PoolView pool;
 };
 hipError_t launch_swap_scan(const SwapScanArgs &a, hipStream_t st);
-hipError_t launch_swap_choose(const SwapSelArgs &a, hipStream_t st);
+// the ins and outs of a frame, or, with late, the outs where moves[1] was -1
+hipError_t launch_swap_choose(const SwapSelArgs &a, bool late, hipStream_t st);
 hipError_t launch_swap_move(int fmt, const SwapMoveArgs &a, hipStream_t st);
 hipError_t launch_swap_init(int32_t *stack, int32_t n_blocks, int32_t *top, int32_t *blk, uint8_t *onhost,
                             int64_t n_entries, hipStream_t st);

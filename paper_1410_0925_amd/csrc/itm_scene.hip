@@ -129,8 +129,9 @@ struct itm_scene {
     SwapCnt *swap_cnt = nullptr;      // [2], one per frame parity
     uint32_t *swap_hist = nullptr;    // [kSwapHistWords]
     SwapSel *swap_sel = nullptr;      // [2][kSwapPasses]
-    int32_t *swap_chosen = nullptr;   // [swap_in_cap + swap_out_cap] entries that move: in, then out
-    int32_t *swap_moves = nullptr;    // [2] how many, pinned
+    int32_t *swap_chosen = nullptr;   // [2 swap_in_cap + swap_out_cap] entries that move: in, out after
+                                      // its merge, out
+    int32_t *swap_moves = nullptr;    // [3] how many of each (SwapSelArgs), pinned
     int32_t swap_parity = 0;
     int32_t swap_in_cap = 0, swap_out_cap = 0;
     // the host copies: pinned voxel blocks (storage form, F then W), one slot each.
@@ -644,9 +645,9 @@ itm_status grow_host_copies(itm_scene *sc, int64_t n_slots)
 // After a frame's integration (section "Swapping"): of the candidates, found on
 // the device, up to swap_in_cap host copies merge into their device blocks and
 // up to swap_out_cap device blocks that were not visible in the frame (and have
-// nothing to merge) move to the host, the first in key order.  Two host
+// nothing to merge then) move to the host, the first in key order.  Two host
 // synchronisations per frame: after the choice, when the host makes room for the
-// copies, and after the moves.
+// copies, and after the moves; a third where the choice takes a second round.
 itm_status swap_frame(itm_scene *sc)
 {
     SwapScanArgs sa;
@@ -670,13 +671,19 @@ itm_status swap_frame(itm_scene *sc)
     se.hist = sc->swap_hist;
     se.sel = sc->swap_sel;
     se.chosen[0] = sc->swap_chosen;
-    se.chosen[1] = sc->swap_chosen + sc->swap_in_cap;
+    se.chosen[1] = sc->swap_chosen + 2 * (size_t)sc->swap_in_cap;
+    se.chosen[2] = sc->swap_chosen + sc->swap_in_cap;
     se.moves = sc->swap_moves;
     HIP_TRY(launch_swap_scan(sa, sc->stream));
-    HIP_TRY(launch_swap_choose(se, sc->stream));
+    HIP_TRY(launch_swap_choose(se, false, sc->stream));
     HIP_TRY(hipStreamSynchronize(sc->stream));
     sc->swap_parity ^= 1;
-    const int32_t n_in = sc->swap_moves[0], n_out = sc->swap_moves[1];
+    if (sc->swap_moves[1] < 0) {
+        HIP_TRY(launch_swap_choose(se, true, sc->stream));
+        HIP_TRY(hipStreamSynchronize(sc->stream));
+    }
+    // n_late: the outs that merge first
+    const int32_t n_in = sc->swap_moves[0], n_out = sc->swap_moves[1], n_late = sc->swap_moves[2];
     SwapMoveArgs ma;
     ma.h = sa.h;
     ma.sdf = sc->sdf;
@@ -699,14 +706,25 @@ itm_status swap_frame(itm_scene *sc)
     const int32_t reused = std::min(n_out, ma.n_free);
     if (itm_status st = grow_host_copies(sc, (int64_t)sc->slot_next + (n_out - reused))) return st;
     HIP_TRY(launch_swap_move(sc->fmt, ma, sc->stream));
-    HIP_TRY(hipStreamSynchronize(sc->stream));
     sc->ring_head += reused;
     sc->ring_tail += n_in;
     sc->slot_next += n_out - reused;
+    if (n_late) {   // into slots that the merges freed
+        ma.chosen[1] = se.chosen[2];
+        ma.n_in = 0;
+        ma.n_out = n_late;
+        ma.ring_head = sc->ring_head;
+        ma.ring_tail = sc->ring_tail;
+        ma.n_free = (int32_t)(sc->ring_tail - sc->ring_head);
+        ma.slot_next = sc->slot_next;
+        HIP_TRY(launch_swap_move(sc->fmt, ma, sc->stream));
+        sc->ring_head += n_late;
+    }
+    HIP_TRY(hipStreamSynchronize(sc->stream));
     sc->swapped_in_last = n_in;
-    sc->swapped_out_last = n_out;
+    sc->swapped_out_last = n_out + n_late;
     sc->swapped_in_total += n_in;
-    sc->swapped_out_total += n_out;
+    sc->swapped_out_total += n_out + n_late;
     return ITM_OK;
 }
 
@@ -1307,12 +1325,12 @@ itm_status itm_scene_enable_swapping(itm_scene *sc, int64_t device_blocks, int32
         dev_alloc((void **)&sc->swap_cnt, sizeof(SwapCnt) * 2, "swap counts") ||
         dev_alloc((void **)&sc->swap_hist, sizeof(uint32_t) * kSwapHistWords, "swap digit counts") ||
         dev_alloc((void **)&sc->swap_sel, sizeof(SwapSel) * 2 * kSwapPasses, "swap choice") ||
-        dev_alloc((void **)&sc->swap_chosen, sizeof(int32_t) * ((size_t)swap_in + swap_out), "swap entries") ||
+        dev_alloc((void **)&sc->swap_chosen, sizeof(int32_t) * (2 * (size_t)swap_in + swap_out), "swap entries") ||
         dev_alloc((void **)&sc->chunk_tab, sizeof(uint8_t *) * (sc->n_entries / kSwapChunk + 1), "host copy table") ||
         dev_alloc((void **)&sc->slot_of, sizeof(int32_t) * sc->n_entries, "host slots") ||
         dev_alloc((void **)&sc->free_ring, sizeof(int32_t) * sc->n_entries, "free host slots"))
         return ITM_ERR_OOM;
-    if (hipHostMalloc((void **)&sc->swap_moves, sizeof(int32_t) * 2) != hipSuccess)
+    if (hipHostMalloc((void **)&sc->swap_moves, sizeof(int32_t) * 3) != hipSuccess)
         return fail(ITM_ERR_OOM, "pinned swap counts");
     hipError_t e = launch_init(sc->buckets, sc->head, sc->n_buckets, sc->excess, sc->n_excess, sc->vis_stamp,
                                sc->n_entries, sc->set, 2 * sc->set_size, sc->occ,

@@ -24,8 +24,9 @@ __device__ __forceinline__ unsigned long long order_key(unsigned long long key)
 
 // The candidates of this frame's transfers, four hash entries per thread.
 //   swap in:  entries holding a device block and a host copy not yet merged;
-//   swap out: entries holding a device block, nothing to merge, not listed in
-//             this frame (stamp != stamp_now).
+//   swap out: entries holding a device block, not listed in this frame (stamp !=
+//             stamp_now), with nothing to merge once the swap-ins are done: one with
+//             a host copy is in both lists, marked, and leaves only if it merges now.
 // Each list gets (order, entry) records.  Thread 0 also resets a pool top that
 // the allocation ran below zero, and the grid clears the counts of the choice.
 //
@@ -55,14 +56,14 @@ __global__ __launch_bounds__(kSwapThreads) void k_swap_scan(SwapScanArgs a)
         }
     }
     // candidates of this thread: in the low half the swap-ins, in the high the swap-outs
-    uint32_t n = 0;
+    uint32_t n = 0, np = 0;
     bool in[4], out[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) {
-        const bool host = (oh >> (8 * k)) & 0xffu;
-        in[k] = b[k] >= 0 && host;
-        out[k] = b[k] >= 0 && !host && st[k] != a.stamp_now;
+        in[k] = b[k] >= 0 && ((oh >> (8 * k)) & 0xffu);
+        out[k] = b[k] >= 0 && st[k] != a.stamp_now;
         n += (uint32_t)in[k] + ((uint32_t)out[k] << 16);
+        np += in[k] && out[k];
     }
     // places within the workgroup: at most 4096 of each, so the halves never carry
     uint32_t incl = n;
@@ -73,7 +74,9 @@ __global__ __launch_bounds__(kSwapThreads) void k_swap_scan(SwapScanArgs a)
     }
     __shared__ uint32_t s_wave[kSwapThreads / kWave];
     __shared__ unsigned long long s_base;
+    __shared__ uint32_t s_pend;
     if (lane == kWave - 1) s_wave[wave] = incl;
+    if (t == 0) s_pend = 0;
     __syncthreads();
     uint32_t before = 0, all = 0;
 #pragma unroll
@@ -82,9 +85,11 @@ __global__ __launch_bounds__(kSwapThreads) void k_swap_scan(SwapScanArgs a)
         all += s_wave[w];
     }
     if (all == 0) return;   // uniform
+    if (np) atomicAdd(&s_pend, np);
     if (t == 0)
         s_base = atomicAdd(&a.cnt->cand, (unsigned long long)(all & 0xffffu) | ((unsigned long long)(all >> 16) << 32));
     __syncthreads();
+    if (t == 0 && s_pend) atomicAdd(&a.cnt->pend, s_pend);
     const uint32_t place = before + incl - n;
     uint32_t pi = (uint32_t)s_base + (place & 0xffffu), po = (uint32_t)(s_base >> 32) + (place >> 16);
 #pragma unroll
@@ -93,8 +98,9 @@ __global__ __launch_bounds__(kSwapThreads) void k_swap_scan(SwapScanArgs a)
         SwapRec r;
         r.key = order_key(entry_key(a.h, (int32_t)(e0 + k)));
         r.e = (int32_t)(e0 + k);
-        r.pad = 0;
-        (in[k] ? a.in_list : a.out_list)[in[k] ? pi++ : po++] = r;
+        r.pend = in[k] && out[k];
+        if (in[k]) a.in_list[pi++] = r;
+        if (out[k]) a.out_list[po++] = r;
     }
 }
 
@@ -146,43 +152,94 @@ __device__ __forceinline__ SwapSel next_digit(const uint32_t *hist, SwapSel s, i
 // them again, which is less than another launch.
 // Launch bound: 4.5 us a pass at 15 k candidates, with 8 to 64 workgroups per list
 // alike; 64 for long lists.
-__global__ __launch_bounds__(kSwapThreads) void k_swap_choose(SwapSelArgs a, int pass)
+//
+// A block that merges in this frame may leave in it.  Where every in is taken, the
+// marked outs all merge.  Where not, those up to the last in's key do: if the outs
+// fit their transfer, pass 4 lists them by that key, else they wait for it, and a
+// second round of the passes (late) chooses them.  (In a VGA frame of a camera that
+// turns, with 2048 + 2048 blocks, one frame in three has marked outs, one in eight a
+// second round.)
+__global__ __launch_bounds__(kSwapThreads) void k_swap_choose(SwapSelArgs a, int pass, bool late)
 {
-    const int t = threadIdx.x, q = blockIdx.y;
-    const uint32_t n = q ? (uint32_t)(a.cnt->cand >> 32) : (uint32_t)a.cnt->cand, cap = (uint32_t)a.cap[q];
+    const int t = threadIdx.x, q = late ? 1 : blockIdx.y;
+    const uint32_t n_in = (uint32_t)a.cnt->cand, pend = a.cnt->pend, cap = (uint32_t)a.cap[q];
+    const uint32_t len = q ? (uint32_t)(a.cnt->cand >> 32) : n_in;
+    const uint32_t n = late ? len - pend + a.cnt->pend_in : len;   // that may qualify
+    const bool some = q && pend > 0 && n_in > (uint32_t)a.cap[0];  // marked outs: not all of them do
+    const bool wait = some && !late && n > cap;
     const bool last = pass == kSwapPasses;
+    const bool drawn = q && pend > 0 && n > 0 && !wait;            // how many move is known when all are listed
     if (last && blockIdx.x == 0 && t == 0) {
-        a.moves[q] = (int32_t)min(n, cap);   // read by the host after the launch
-        if (q == 0) a.cnt_next->cand = 0;    // the next frame's counts
-        a.cnt_next->chosen[q] = 0;
+        if (!drawn) {   // read by the host after the launch
+            a.moves[q] = wait ? -1 : (int32_t)min(n, cap);
+            if (q) a.moves[2] = 0;
+        }
+        if (!late) {    // the next frame's counts
+            if (q) a.cnt_next->out = 0;
+            else {
+                a.cnt_next->cand = 0;
+                a.cnt_next->pend = a.cnt_next->pend_in = a.cnt_next->in = 0;
+            }
+        }
     }
-    if (n == 0 || (!last && n <= cap)) return;
+    if (n == 0 || wait || (!last && n <= cap)) return;
     SwapSel s;
     s.prefix = 0;
     s.rem = cap;
     if (n > cap && pass > 0) {
         if (pass > 1) s = a.sel[q * kSwapPasses + pass - 1];
         s = next_digit(a.hist + ((q * kSwapPasses + pass - 1) << kSwapDigit), s, t);
-        if (!last && blockIdx.x == 0 && t == 0) a.sel[q * kSwapPasses + pass] = s;
+        // (place 0 of list 0 is free: it takes the finished key)
+        if (blockIdx.x == 0 && t == 0 && (!last || q == 0)) a.sel[last ? 0 : q * kSwapPasses + pass] = s;
     }
+    // the largest key that merges: marked outs above it do not qualify
+    unsigned long long top_in = ~0ull;
+    if (some)
+        top_in = late ? a.sel[0].prefix
+                      : next_digit(a.hist + ((kSwapPasses - 1) << kSwapDigit), a.sel[kSwapPasses - 1], t).prefix;
     const SwapRec *list = a.list[q];
     const uint32_t stride = gridDim.x * kSwapThreads;
     if (last) {
         const unsigned long long top = n > cap ? s.prefix : ~0ull;
         const int lane = t & (kWave - 1);
-        for (uint32_t i0 = blockIdx.x * kSwapThreads; i0 < n; i0 += stride) {
+        const unsigned long long below = (1ull << lane) - 1;
+        for (uint32_t i0 = blockIdx.x * kSwapThreads; i0 < len; i0 += stride) {
             const uint32_t i = i0 + t;
             SwapRec r;
             r.key = ~0ull;
             r.e = -1;
-            if (i < n) r = list[i];
-            const bool take = i < n && r.key <= top;
-            const unsigned long long m = __ballot(take);
+            r.pend = 0;
+            if (i < len) r = list[i];
+            const bool take = i < len && r.key <= top && !(r.pend && r.key > top_in);
+            const unsigned long long m = __ballot(take), mp = __ballot(take && r.pend);
             if (m == 0) continue;
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(&a.cnt->chosen[q], (uint32_t)__popcll(m));
-            base = __builtin_amdgcn_readfirstlane(base);
-            if (take) a.chosen[q][base + __popcll(m & ((1ull << lane) - 1))] = r.e;
+            // the wave's lanes draw their places together
+            unsigned long long base = 0;
+            if (q == 0) {
+                if (lane == 0) {
+                    base = atomicAdd(&a.cnt->in, (uint32_t)__popcll(m));
+                    if (mp) atomicAdd(&a.cnt->pend_in, (uint32_t)__popcll(mp));
+                }
+                base = __builtin_amdgcn_readfirstlane((uint32_t)base);
+                if (take) a.chosen[0][base + __popcll(m & below)] = r.e;
+            } else {
+                if (lane == 0)
+                    base = atomicAdd(&a.cnt->out, (unsigned long long)__popcll(m & ~mp) |
+                                                      (unsigned long long)__popcll(mp) << 24);
+                base = __shfl(base, 0, kWave);
+                if (take && r.pend) a.chosen[2][(base >> 24 & 0xffffff) + __popcll(mp & below)] = r.e;
+                else if (take) a.chosen[1][(base & 0xffffff) + __popcll(m & ~mp & below)] = r.e;
+            }
+        }
+        if (drawn) {   // the last workgroup tells the host (one word: no fence between the counts)
+            __syncthreads();
+            if (t == 0) {
+                const unsigned long long o = atomicAdd(&a.cnt->out, 1ull << 48);
+                if ((o >> 48) == gridDim.x - 1) {
+                    a.moves[1] = (int32_t)(o & 0xffffff);
+                    a.moves[2] = (int32_t)(o >> 24 & 0xffffff);
+                }
+            }
         }
         return;
     }
@@ -190,9 +247,11 @@ __global__ __launch_bounds__(kSwapThreads) void k_swap_choose(SwapSelArgs a, int
     for (int i = t; i < 1 << kSwapDigit; i += kSwapThreads) s_cnt[i] = 0;
     __syncthreads();
     const int low = kSwapDigit * (kSwapPasses - 1 - pass);
-    for (uint32_t i = blockIdx.x * kSwapThreads + t; i < n; i += stride) {
-        const unsigned long long k = list[i].key >> low;
-        if ((k >> kSwapDigit) == s.prefix) atomicAdd(&s_cnt[k & ((1 << kSwapDigit) - 1)], 1u);
+    for (uint32_t i = blockIdx.x * kSwapThreads + t; i < len; i += stride) {
+        const SwapRec r = list[i];
+        const unsigned long long k = r.key >> low;
+        if ((k >> kSwapDigit) == s.prefix && !(r.pend && r.key > top_in))
+            atomicAdd(&s_cnt[k & ((1 << kSwapDigit) - 1)], 1u);
     }
     __syncthreads();
     uint32_t *hist = a.hist + ((q * kSwapPasses + pass) << kSwapDigit);
@@ -200,10 +259,10 @@ __global__ __launch_bounds__(kSwapThreads) void k_swap_choose(SwapSelArgs a, int
         if (s_cnt[i]) atomicAdd(&hist[i], s_cnt[i]);
 }
 
-hipError_t launch_swap_choose(const SwapSelArgs &a, hipStream_t st)
+hipError_t launch_swap_choose(const SwapSelArgs &a, bool late, hipStream_t st)
 {
     for (int pass = 0; pass <= kSwapPasses; pass++)
-        k_swap_choose<<<dim3(kSwapChooseWgs, 2), kSwapThreads, 0, st>>>(a, pass);
+        k_swap_choose<<<dim3(kSwapChooseWgs, late ? 1 : 2), kSwapThreads, 0, st>>>(a, pass, late);
     return hipGetLastError();
 }
 
@@ -214,8 +273,9 @@ hipError_t launch_swap_choose(const SwapSelArgs &a, hipStream_t st)
 //        (unchanged when both weights are 0); the copy's slot is free afterwards;
 //   out: the device block's voxels go to a host slot, the block is reset (F = 1,
 //        W = 0) and returned to the pool, and the entry has its data on the host.
-// Slots freed here are used from the next frame on, so no wave writes a slot that
-// another reads.
+// Slots freed by a launch are used from the next one on, so no wave writes a slot
+// that another reads.  Blocks that merge and leave in the same frame are among the
+// ins of its first launch and the outs of a second.
 //
 // Bound by the link to the host.  Ins and outs alternate, so that it carries both
 // directions at once; every access to a host copy is 16 B per lane, a wave's

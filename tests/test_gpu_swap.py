@@ -133,3 +133,22 @@ def test_the_choice_at_its_edges(fmt, swap_in, swap_out):
            "s16u8": lambda W: (0.5 / 32767 + 4 * 2.0 ** -23) * (np.asarray(W, np.float64) + 1) + 1e-6}[fmt]
     compare_volumes(g.export(), o.export(), tol=tol, cands=o.export_candidates())
     g.close()
+
+
+@pytest.mark.parametrize("fmt,swap_in,swap_out,stride", [("s16u8", 2, 43, 1), ("f32", 5, 9, 1), ("f32", 2, 3, 13),
+                                                         ("f16", 2, 43, 13), ("f32", 20, 30, 13), ("s16u8", 60, 70, 13)])
+def test_blocks_that_merge_and_leave_in_one_frame(fmt, swap_in, swap_out, stride):
+    """Transfers smaller than what is pending, over a camera that jumps about: a host copy
+    that waited until its block was out of view merges and, with nothing left to merge,
+    may leave in the same frame -- with every pending copy merged in it or only some,
+    with room in the transfer or not.  Numbers moved per frame and volume as above."""
+    itm, torch = gpu()
+    st = make_stream("tiny", n_frames=40 if stride == 1 else 60)
+    order = [(stride * k) % st.n_frames for k in range(40)]
+    st.depth, st.T_wc = st.depth[order], st.T_wc[order]
+    print(f"case: tiny, every {stride}th frame, {fmt}, transfers of {swap_in} and {swap_out} blocks", flush=True)
+    g, o, _ = run_both(st, 40, 4096, swap_in, swap_out, fmt=fmt)
+    tol = {"f32": 1e-5, "f16": lambda W: 2.0 ** -11 * (np.asarray(W, np.float64) + 1) + 1e-5,
+           "s16u8": lambda W: (0.5 / 32767 + 4 * 2.0 ** -23) * (np.asarray(W, np.float64) + 1) + 1e-6}[fmt]
+    compare_volumes(g.export(), o.export(), tol=tol, cands=o.export_candidates())
+    g.close()
