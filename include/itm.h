@@ -346,8 +346,8 @@ itm_status itm_track_noalloc(itm_scene *scene, const float *depth, const itm_int
 /* The host copies are in pinned memory (8 MiB or less at a time as they come  */
 /* to be needed, kept until the scene is destroyed; ITM_ERR_OOM, with the frame */
 /* fused and nothing moved, when there is no more), which the device reads and */
-/* writes directly; each frame synchronises the stream twice, a third time    */
-/* where what merges decides what may leave.                                  */
+/* writes directly.  Each frame synchronises the stream twice, once more where */
+/* it takes more of that memory and where what merges decides what may leave. */
 /* The raycast sees the blocks on the device only; itm_export_blocks returns    */
 /* every block wherever it is (merged when both copies exist).  Call before   */
 /* the first frame; not with colour, a refiner or itm_import_blocks            */

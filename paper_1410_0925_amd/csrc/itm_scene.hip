@@ -138,6 +138,7 @@ struct itm_scene {
     // A slot belongs to one entry or is in the ring of free slots, so there are
     // never more than entries.
     std::vector<uint8_t *> host_chunks;   // kSwapChunk slots each
+    size_t chunks_sent = 0;           // of their pointers, how many chunk_tab holds
     uint8_t **chunk_tab = nullptr;    // the same pointers, on the device
     int32_t *slot_of = nullptr;       // [n_entries] slot of the entry's host copy (where onhost)
     int32_t *free_ring = nullptr;     // [n_entries] free slots
@@ -619,27 +620,29 @@ itm_status refine_visible(itm_scene *sc)
     return ITM_OK;
 }
 
-// pinned host memory for the first n_slots slots of host copies
+// pinned host memory for the first n_slots slots of host copies, known to the device
 itm_status grow_host_copies(itm_scene *sc, int64_t n_slots)
 {
     const size_t bytes = (sdf_elem(sc->fmt) + w_elem(sc->fmt)) * kBlockVox * (size_t)kSwapChunk;
-    const size_t had = sc->host_chunks.size(), want = (size_t)((n_slots + kSwapChunk - 1) / kSwapChunk);
-    if (want <= had) return ITM_OK;
+    const size_t want = (size_t)((n_slots + kSwapChunk - 1) / kSwapChunk);
     while (sc->host_chunks.size() < want) {
         uint8_t *p = nullptr;
         if (hipHostMalloc((void **)&p, bytes) != hipSuccess) {
             (void)hipGetLastError();
-            break;
+            return fail(ITM_ERR_OOM, "pinned host copies of %lld blocks", (long long)n_slots);
         }
         sc->host_chunks.push_back(p);
     }
-    const size_t got = sc->host_chunks.size();
-    if (got > had) {   // complete on return: a later growth may move the vector
-        HIP_TRY(hipMemcpyAsync(sc->chunk_tab + had, sc->host_chunks.data() + had, sizeof(uint8_t *) * (got - had),
+    // what an earlier frame could not send goes over too: no slot below n_slots may
+    // lie in a chunk that the device does not know
+    const size_t first = sc->chunks_sent, n = sc->host_chunks.size();
+    if (first < n) {   // complete on return: a later growth may move the vector
+        HIP_TRY(hipMemcpyAsync(sc->chunk_tab + first, sc->host_chunks.data() + first, sizeof(uint8_t *) * (n - first),
                                hipMemcpyHostToDevice, sc->stream));
         HIP_TRY(hipStreamSynchronize(sc->stream));
+        sc->chunks_sent = n;
     }
-    return got < want ? fail(ITM_ERR_OOM, "pinned host copies of %lld blocks", (long long)n_slots) : ITM_OK;
+    return ITM_OK;
 }
 
 // After a frame's integration (section "Swapping"): of the candidates, found on
@@ -647,9 +650,11 @@ itm_status grow_host_copies(itm_scene *sc, int64_t n_slots)
 // up to swap_out_cap device blocks that were not visible in the frame (and have
 // nothing to merge then) move to the host, the first in key order.  Two host
 // synchronisations per frame: after the choice, when the host makes room for the
-// copies, and after the moves; a third where the choice takes a second round.
+// copies, and after the moves; one more where the choice takes a second round, and
+// where room for the copies is allocated.
 itm_status swap_frame(itm_scene *sc)
 {
+    sc->swapped_in_last = sc->swapped_out_last = 0;   // until the moves are done
     SwapScanArgs sa;
     sa.h = hash_view(sc);
     sa.stamp = sc->vis_stamp;

@@ -1,0 +1,54 @@
+/* The HIP calls through which the library takes memory and sends it pointers, with limits
+ * that a test sets: loaded before everything else, these come first in the lookup of
+ * their names and pass on to the runtime what the limits allow.  A refused call changes
+ * nothing and returns the runtime's own error code. */
+#define _GNU_SOURCE
+#include <dlfcn.h>
+#include <stddef.h>
+
+typedef int (*malloc_t)(void **, size_t);
+typedef int (*host_malloc_t)(void **, size_t, unsigned);
+typedef int (*copy_t)(void *, const void *, size_t, int, void *);
+
+/* hipErrorOutOfMemory, hipErrorUnknown, hipMemcpyHostToDevice */
+enum { kOutOfMemory = 2, kUnknown = 999, kHostToDevice = 1 };
+
+static size_t host_from = (size_t)-1, dev_from = (size_t)-1, copy_to = 0;
+static long host_left = 0, dev_left = 0, copy_left = 0, refused = 0;
+
+/* pinned (device) allocations of at least `from` bytes: `left` more succeed */
+void limit_host(size_t from, long left) { host_from = from; host_left = left; }
+void limit_device(size_t from, long left) { dev_from = from; dev_left = left; }
+/* copies to the device of at most `to` bytes: the next `n` fail */
+void fail_copies(size_t to, long n) { copy_to = to; copy_left = n; }
+/* calls refused since last asked */
+long refusals(void)
+{
+    long n = refused;
+    refused = 0;
+    return n;
+}
+
+static void *runtime(const char *name)
+{
+    void *lib = dlopen("libamdhip64.so.7", RTLD_NOW | RTLD_NOLOAD);
+    return lib ? dlsym(lib, name) : NULL;
+}
+
+int hipHostMalloc(void **p, size_t n, unsigned flags)
+{
+    if (n >= host_from && host_left-- <= 0) return refused++, kOutOfMemory;
+    return ((host_malloc_t)runtime("hipHostMalloc"))(p, n, flags);
+}
+
+int hipMalloc(void **p, size_t n)
+{
+    if (n >= dev_from && dev_left-- <= 0) return refused++, kOutOfMemory;
+    return ((malloc_t)runtime("hipMalloc"))(p, n);
+}
+
+int hipMemcpyAsync(void *dst, const void *src, size_t n, int kind, void *stream)
+{
+    if (kind == kHostToDevice && n <= copy_to && copy_left > 0) return copy_left--, refused++, kUnknown;
+    return ((copy_t)runtime("hipMemcpyAsync"))(dst, src, n, kind, stream);
+}

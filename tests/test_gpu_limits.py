@@ -1,0 +1,113 @@
+"""What the library does where memory or a transfer is refused.  The refusals are made
+on the host, by limited_hip.c in front of the HIP runtime, in one process of their own
+(this file, run as a program); every kernel runs to its normal end."""
+import ctypes as C
+import json
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.gpu
+
+
+def _swapping(itm, torch, st, frames, each=None, fmt="f32", pool=40000, swap_in=500, swap_out=300):
+    """st's frames fused with swapping; each(scene, f) before frame f.  The exported map,
+    the numbers moved and the frames that failed."""
+    K = tuple(st.intrinsics) + (st.width, st.height)
+    sc = itm.Scene.from_params(st.params, fmt=fmt)
+    sc.enable_swapping(pool, swap_in, swap_out)
+    stats, failed = [], []
+    for f in range(frames):
+        if each:
+            each(sc, f)
+        try:
+            sc.integrate(torch.from_numpy(st.depth[f]).cuda(), K, st.T_wc[f])
+        except itm.ItmError as e:
+            failed.append((f, str(e)))
+        stats.append(sc.swap_stats())
+    out = sc.export()
+    sc.close()
+    return out, stats, failed
+
+
+def _same(a, b):
+    return all(np.array_equal(x.view(np.uint32), y.view(np.uint32)) for x, y in zip(a, b))
+
+
+def pointers_not_sent(itm, torch, hip, st):
+    """The host copies' second memory (from 2049 copies on) is there, but its pointer does
+    not reach the device in one frame: that frame moves nothing and says so, and the
+    next one sends the pointer before any block goes there."""
+    at = [None]
+
+    def each(sc, f):
+        if at[0] is None and sc.swap_stats()["n_host_only"] + 300 > 2048:
+            at[0] = f
+            hip.fail_copies(8, 1)      # the pointer is the only copy of 8 bytes
+    (_, _, _), stats, failed = got = _swapping(itm, torch, st, 20, each)
+    assert at[0] is not None and hip.refusals() == 1
+    assert len(failed) == 1 and failed[0][0] == at[0], failed
+    f = failed[0][0]
+    s = stats[f]
+    assert s["swapped_in_last"] == s["swapped_out_last"] == 0
+    assert s["swapped_out_total"] == stats[f - 1]["swapped_out_total"]
+    assert stats[f + 1]["n_host_only"] > 2048
+    # a frame without moves only delays them: the map holds the same blocks and, once
+    # merged, every sample (the averages are joined in another order)
+    c, F, W = _swapping(itm, torch, st, 20)[0]
+    assert np.array_equal(got[0][0], c) and np.array_equal(got[0][2], W)
+    assert np.abs(got[0][1] - F).max() < 1e-5
+
+
+CASES = {f.__name__: f for f in (pointers_not_sent,)}
+
+
+@pytest.fixture(scope="module")
+def outcomes(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("limits") / "limited_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "limited_hip.c"), "-ldl"],
+                   check=True)
+    p = subprocess.run([sys.executable, "-u", os.path.abspath(__file__), so], cwd=ROOT, capture_output=True, text=True,
+                       timeout=110)
+    print(p.stdout[-4000:], p.stderr[-4000:], flush=True)
+    got = dict(json.loads(x[6:]) for x in p.stdout.splitlines() if x.startswith("CASE: "))
+    assert p.returncode == 0, (p.returncode, got)
+    return got
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_refused(name, outcomes):
+    assert outcomes.get(name) == "ok", outcomes.get(name)
+
+
+if __name__ == "__main__":
+    hip = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)     # before the runtime is loaded
+    for name in ("limit_host", "limit_device", "fail_copies"):
+        getattr(hip, name).argtypes = [C.c_size_t, C.c_long]
+    hip.refusals.restype = C.c_long
+    sys.path.insert(0, ROOT)
+    import traceback
+
+    import torch
+
+    import paper_1410_0925_amd as itm
+    from synth import make_stream
+    st = make_stream("vga", n_frames=40)
+    for name, case in CASES.items():
+        if len(sys.argv) > 2 and name not in sys.argv[2:]:
+            continue
+        print("begin", name, flush=True)
+        hip.refusals()
+        try:
+            case(itm, torch, hip, st)
+            res = "ok"
+        except Exception:
+            res = traceback.format_exc()
+        hip.limit_host(2 ** 63, 0)
+        hip.limit_device(2 ** 63, 0)
+        hip.fail_copies(0, 0)
+        print("CASE: " + json.dumps([name, res]), flush=True)
