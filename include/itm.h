@@ -343,11 +343,14 @@ itm_status itm_track_noalloc(itm_scene *scene, const float *depth, const itm_int
 /*    merge any more, the first swap_out in key order move to the host (a host */
 /*    voxel block per hash entry, kept by the library) and free their device   */
 /*    block.                                                                   */
-/* The host copies are in pinned memory (8 MiB or less at a time as they come  */
-/* to be needed, kept until the scene is destroyed; ITM_ERR_OOM, with the frame */
-/* fused and nothing moved, when there is no more), which the device reads and */
-/* writes directly.  Each frame synchronises the stream twice, once more where */
-/* it takes more of that memory and where what merges decides what may leave. */
+/* The host copies are in pinned memory, taken 2048 blocks at a time (8 MiB or  */
+/* less) as they come to be needed and kept until the scene is destroyed, which */
+/* the device reads and writes directly.  Where there is no more of it, further */
+/* copies take pageable memory, and from then on all moves go through 2048      */
+/* pinned blocks, with host copies and synchronisations of their own;          */
+/* ITM_ERR_OOM, with the frame fused and nothing moved, when neither is left.   */
+/* Otherwise a frame synchronises the stream twice, once more where it takes    */
+/* memory and where what merges decides what may leave.                        */
 /* The raycast sees the blocks on the device only; itm_export_blocks returns    */
 /* every block wherever it is (merged when both copies exist).  Call before   */
 /* the first frame; not with colour, a refiner or itm_import_blocks            */

@@ -459,6 +459,7 @@ struct SwapMoveArgs {
     uint8_t *onhost;
     int32_t *slot_of;         // per entry, the slot of its host copy
     uint8_t *const *chunks;   // host memory of the slots, kSwapChunk each
+    uint8_t *xfer;            // if set, block i's copy goes to or comes from here instead
     int32_t *free_ring;       // free slots, first in first out
     int64_t ring_head, ring_tail, ring_size;
     int32_t n_free;           // free slots before this frame; further outs take

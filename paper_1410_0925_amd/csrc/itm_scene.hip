@@ -134,11 +134,14 @@ struct itm_scene {
     int32_t *swap_moves = nullptr;    // [3] how many of each (SwapSelArgs), pinned
     int32_t swap_parity = 0;
     int32_t swap_in_cap = 0, swap_out_cap = 0;
-    // the host copies: pinned voxel blocks (storage form, F then W), one slot each.
-    // A slot belongs to one entry or is in the ring of free slots, so there are
-    // never more than entries.
+    // the host copies: voxel blocks (storage form, F then W), one slot each, pinned
+    // while there is pinned memory.  A slot belongs to one entry or is in the ring of
+    // free slots, so there are never more than entries.
     std::vector<uint8_t *> host_chunks;   // kSwapChunk slots each
+    size_t chunks_pinned = 0;         // the first of them; the rest is pageable
     size_t chunks_sent = 0;           // of their pointers, how many chunk_tab holds
+    uint8_t *xfer = nullptr;          // with pageable chunks: kSwapChunk blocks pinned, all moves' way
+    std::vector<int32_t> xfer_ent, xfer_slot;   // host lists of such moves
     uint8_t **chunk_tab = nullptr;    // the same pointers, on the device
     int32_t *slot_of = nullptr;       // [n_entries] slot of the entry's host copy (where onhost)
     int32_t *free_ring = nullptr;     // [n_entries] free slots
@@ -225,7 +228,10 @@ void release(itm_scene *sc)
                     (void *)sc->chunk_tab, (void *)sc->slot_of, (void *)sc->free_ring})
         (void)hipFree(p);
     if (sc->swap_moves) (void)hipHostFree(sc->swap_moves);
-    for (uint8_t *p : sc->host_chunks) (void)hipHostFree(p);
+    for (size_t i = 0; i < sc->host_chunks.size(); i++)
+        if (i < sc->chunks_pinned) (void)hipHostFree(sc->host_chunks[i]);
+        else std::free(sc->host_chunks[i]);
+    if (sc->xfer) (void)hipHostFree(sc->xfer);
     delete sc;
 }
 
@@ -620,27 +626,100 @@ itm_status refine_visible(itm_scene *sc)
     return ITM_OK;
 }
 
-// pinned host memory for the first n_slots slots of host copies, known to the device
+// bytes of a swapped-out block's host copy, and where slot's lies
+size_t copy_bytes(const itm_scene *sc) { return (sdf_elem(sc->fmt) + w_elem(sc->fmt)) * kBlockVox; }
+uint8_t *host_copy(const itm_scene *sc, int32_t slot)
+{
+    return sc->host_chunks[slot / kSwapChunk] + (size_t)(slot % kSwapChunk) * copy_bytes(sc);
+}
+
+// The last pinned chunk becomes the way of all moves, what it held pageable: from
+// here on copies take pageable memory.  False without memory (nothing is changed).
+bool give_up_pinning(itm_scene *sc, size_t bytes)
+{
+    uint8_t *p = sc->chunks_pinned ? (uint8_t *)std::malloc(bytes) : nullptr;
+    if (!p) return false;
+    try {
+        sc->xfer_ent.resize(std::max(sc->swap_in_cap, sc->swap_out_cap));
+        sc->xfer_slot.resize(sc->n_entries);
+    } catch (const std::bad_alloc &) {
+        std::free(p);
+        return false;
+    }
+    sc->xfer = sc->host_chunks[--sc->chunks_pinned];
+    std::memcpy(p, sc->xfer, bytes);
+    sc->host_chunks[sc->chunks_pinned] = p;
+    return true;
+}
+
+// host memory for the first n_slots slots of host copies, known to the device where
+// it reads and writes them itself
 itm_status grow_host_copies(itm_scene *sc, int64_t n_slots)
 {
-    const size_t bytes = (sdf_elem(sc->fmt) + w_elem(sc->fmt)) * kBlockVox * (size_t)kSwapChunk;
+    const size_t bytes = copy_bytes(sc) * (size_t)kSwapChunk;
     const size_t want = (size_t)((n_slots + kSwapChunk - 1) / kSwapChunk);
     while (sc->host_chunks.size() < want) {
         uint8_t *p = nullptr;
-        if (hipHostMalloc((void **)&p, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(ITM_ERR_OOM, "pinned host copies of %lld blocks", (long long)n_slots);
+        if (!sc->xfer && hipHostMalloc((void **)&p, bytes) == hipSuccess) {
+            sc->host_chunks.push_back(p);
+            sc->chunks_pinned++;
+            continue;
         }
+        if (!sc->xfer) (void)hipGetLastError();
+        if ((!sc->xfer && !give_up_pinning(sc, bytes)) || !(p = (uint8_t *)std::malloc(bytes)))
+            return fail(ITM_ERR_OOM, "host copies of %lld blocks", (long long)n_slots);
         sc->host_chunks.push_back(p);
     }
     // what an earlier frame could not send goes over too: no slot below n_slots may
     // lie in a chunk that the device does not know
     const size_t first = sc->chunks_sent, n = sc->host_chunks.size();
-    if (first < n) {   // complete on return: a later growth may move the vector
+    if (!sc->xfer && first < n) {   // complete on return: a later growth may move the vector
         HIP_TRY(hipMemcpyAsync(sc->chunk_tab + first, sc->host_chunks.data() + first, sizeof(uint8_t *) * (n - first),
                                hipMemcpyHostToDevice, sc->stream));
         HIP_TRY(hipStreamSynchronize(sc->stream));
         sc->chunks_sent = n;
+    }
+    return ITM_OK;
+}
+
+// The moves.  With pageable copies, which the device cannot reach, they go through the
+// pinned blocks of xfer, batch by batch: the ins' copies are put there before a
+// launch, the outs' taken from there after it, their slots read back.
+itm_status move_blocks(itm_scene *sc, const SwapMoveArgs &ma)
+{
+    if (!sc->xfer) {
+        HIP_TRY(launch_swap_move(sc->fmt, ma, sc->stream));
+        return ITM_OK;
+    }
+    const size_t bytes = copy_bytes(sc);
+    for (int out = 0; out < 2; out++) {
+        const int32_t n = out ? ma.n_out : ma.n_in;
+        if (n == 0) continue;
+        HIP_TRY(hipMemcpyAsync(sc->xfer_ent.data(), ma.chosen[out], sizeof(int32_t) * n, hipMemcpyDeviceToHost,
+                               sc->stream));
+        for (int32_t off = 0; off < n; off += kSwapChunk) {
+            const int32_t m = std::min(n - off, kSwapChunk);
+            const int32_t *ent = sc->xfer_ent.data() + off;
+            SwapMoveArgs a = ma;
+            a.xfer = sc->xfer;
+            a.chosen[out] += off;
+            a.n_in = out ? 0 : m;
+            a.n_out = out ? m : 0;
+            a.ring_head += out ? off : 0;
+            a.ring_tail += out ? 0 : off;
+            a.n_free -= out ? off : 0;   // (below 0: counted on from slot_next)
+            if (out) HIP_TRY(launch_swap_move(sc->fmt, a, sc->stream));
+            if (out || off == 0)
+                HIP_TRY(hipMemcpyAsync(sc->xfer_slot.data(), sc->slot_of, sizeof(int32_t) * sc->n_entries,
+                                       hipMemcpyDeviceToHost, sc->stream));
+            HIP_TRY(hipStreamSynchronize(sc->stream));
+            for (int32_t i = 0; i < m; i++) {
+                uint8_t *copy = host_copy(sc, sc->xfer_slot[ent[i]]), *x = sc->xfer + (size_t)i * bytes;
+                std::memcpy(out ? copy : x, out ? x : copy, bytes);
+            }
+            if (!out) HIP_TRY(launch_swap_move(sc->fmt, a, sc->stream));
+        }
+        HIP_TRY(hipStreamSynchronize(sc->stream));   // the lists and xfer are used again
     }
     return ITM_OK;
 }
@@ -700,6 +779,7 @@ itm_status swap_frame(itm_scene *sc)
     ma.onhost = sc->onhost;
     ma.slot_of = sc->slot_of;
     ma.chunks = sc->chunk_tab;
+    ma.xfer = nullptr;
     ma.free_ring = sc->free_ring;
     ma.ring_head = sc->ring_head;
     ma.ring_tail = sc->ring_tail;
@@ -710,7 +790,7 @@ itm_status swap_frame(itm_scene *sc)
     ma.pool = sa.pool;
     const int32_t reused = std::min(n_out, ma.n_free);
     if (itm_status st = grow_host_copies(sc, (int64_t)sc->slot_next + (n_out - reused))) return st;
-    HIP_TRY(launch_swap_move(sc->fmt, ma, sc->stream));
+    if (itm_status st = move_blocks(sc, ma)) return st;
     sc->ring_head += reused;
     sc->ring_tail += n_in;
     sc->slot_next += n_out - reused;
@@ -722,7 +802,7 @@ itm_status swap_frame(itm_scene *sc)
         ma.ring_tail = sc->ring_tail;
         ma.n_free = (int32_t)(sc->ring_tail - sc->ring_head);
         ma.slot_next = sc->slot_next;
-        HIP_TRY(launch_swap_move(sc->fmt, ma, sc->stream));
+        if (itm_status st = move_blocks(sc, ma)) return st;
         sc->ring_head += n_late;
     }
     HIP_TRY(hipStreamSynchronize(sc->stream));
@@ -1265,12 +1345,10 @@ itm_status itm_export_blocks(itm_scene *sc, int32_t *coords, float *sdf, float *
     (void)hipFree(d_w);
     if (st) return st;
     if (e != hipSuccess) return fail(ITM_ERR_HIP, "export failed: %s", hipGetErrorString(e));
-    const size_t blk_bytes = (es + ew) * kBlockVox;
     for (int64_t i = 0; i < n; i++) {
         const size_t src = (size_t)i * kBlockVox;
         const int32_t db = dblk[ent[i]], slot = onh[ent[i]] ? slots[ent[i]] : -1;
-        const uint8_t *host =
-            slot >= 0 ? sc->host_chunks[slot / kSwapChunk] + (size_t)(slot % kSwapChunk) * blk_bytes : nullptr;
+        const uint8_t *host = slot >= 0 ? host_copy(sc, slot) : nullptr;
         for (int l = 0; l < kBlockVox; l++) {
             float f = 1.0f, wf = 0.0f;
             if (db >= 0) {   // the device copy

@@ -267,7 +267,8 @@ hipError_t launch_swap_choose(const SwapSelArgs &a, bool late, hipStream_t st)
 }
 
 // The moves, one wave per block, between the pool and the blocks' host copies
-// (pinned memory that the device reads and writes directly; F then W).
+// (pinned memory that the device reads and writes directly; F then W), or, where some
+// copies are not pinned, xfer.
 //   in:  the host copy merges into the entry's device block,
 //          W = W_d + W_h; F = (W_d F_d + W_h F_h) / W, W = min(W, max_w)
 //        (unchanged when both weights are 0); the copy's slot is free afterwards;
@@ -308,7 +309,9 @@ __global__ __launch_bounds__(256) void k_swap_move(SwapMoveArgs a)
             slot = a.slot_of[e];
         else
             slot = i < a.n_free ? a.free_ring[(a.ring_head + i) % a.ring_size] : a.slot_next + (i - a.n_free);
-        uint8_t *host = a.chunks[slot / kSwapChunk] + (size_t)(slot % kSwapChunk) * (sizeof(S) + sizeof(Wt)) * kBlockVox;
+        constexpr size_t kBytes = (sizeof(S) + sizeof(Wt)) * kBlockVox;
+        uint8_t *host = a.xfer ? a.xfer + (size_t)i * kBytes
+                               : a.chunks[slot / kSwapChunk] + (size_t)(slot % kSwapChunk) * kBytes;
         SV *hs = (SV *)host;
         WV *hw = (WV *)(host + sizeof(S) * kBlockVox);
         SV *ds = (SV *)(sdf + (int64_t)b * kBlockVox);

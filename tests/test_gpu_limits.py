@@ -14,9 +14,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 pytestmark = pytest.mark.gpu
 
 
-def _swapping(itm, torch, st, frames, each=None, fmt="f32", pool=40000, swap_in=500, swap_out=300):
-    """st's frames fused with swapping; each(scene, f) before frame f.  The exported map,
-    the numbers moved and the frames that failed."""
+def _swapping(itm, torch, st, frames, each=None, fmt="f32", pool=40000, swap_in=500, swap_out=300, stride=1):
+    """st's frames (every stride-th, around) fused with swapping; each(scene, f) before
+    frame f.  The exported map, the numbers moved and the frames that failed."""
     K = tuple(st.intrinsics) + (st.width, st.height)
     sc = itm.Scene.from_params(st.params, fmt=fmt)
     sc.enable_swapping(pool, swap_in, swap_out)
@@ -25,7 +25,8 @@ def _swapping(itm, torch, st, frames, each=None, fmt="f32", pool=40000, swap_in=
         if each:
             each(sc, f)
         try:
-            sc.integrate(torch.from_numpy(st.depth[f]).cuda(), K, st.T_wc[f])
+            k = stride * f % st.n_frames
+            sc.integrate(torch.from_numpy(st.depth[k]).cuda(), K, st.T_wc[k])
         except itm.ItmError as e:
             failed.append((f, str(e)))
         stats.append(sc.swap_stats())
@@ -63,7 +64,43 @@ def pointers_not_sent(itm, torch, hip, st):
     assert np.abs(got[0][1] - F).max() < 1e-5
 
 
-CASES = {f.__name__: f for f in (pointers_not_sent,)}
+def _pageable(itm, torch, hip, st, pinned, fmt, swap_in, swap_out):
+    args = dict(fmt=fmt, swap_in=swap_in, swap_out=swap_out, stride=13)
+    want, stats, _ = _swapping(itm, torch, st, 30, **args)
+    assert max(s["n_host_only"] for s in stats) > 4096 and stats[-1]["swapped_in_total"] > 2048
+    hip.limit_host(1 << 20, pinned)
+    got, same, failed = _swapping(itm, torch, st, 30, **args)
+    assert hip.refusals() == 1 and not failed      # it does not ask again
+    assert same == stats and _same(got, want)
+
+
+def pageable_after_one(itm, torch, hip, st):
+    """With pinned memory for 2048 host copies the others take pageable memory: the same
+    blocks move, in batches of 2048 and the rest, and the map is the same bits."""
+    _pageable(itm, torch, hip, st, 1, "f32", 4000, 5000)
+
+
+def pageable_after_two(itm, torch, hip, st):
+    """As above for 4096 copies, in the 3-byte form and with blocks that merge and leave
+    in one frame."""
+    _pageable(itm, torch, hip, st, 2, "s16u8", 250, 3000)
+
+
+def no_copies_at_all(itm, torch, hip, st):
+    """Without any pinned memory a frame that has blocks to move out fuses, moves
+    nothing and says so; once there is memory the blocks move."""
+    def each(sc, f):
+        if f in (0, 10):
+            hip.limit_host(1 << 20 if f == 0 else 2 ** 63, 0)
+    (c, F, W), stats, failed = _swapping(itm, torch, st, 20, each)
+    assert failed and failed[-1][0] == 9 and all("host copies" in e for _, e in failed)
+    assert all(s["swapped_out_total"] == s["swapped_in_total"] == s["n_host_only"] == 0 for s in stats[:10])
+    assert stats[10]["swapped_out_last"] == 300
+    want = _swapping(itm, torch, st, 20)[0]
+    assert np.array_equal(c, want[0]) and np.array_equal(W, want[2]) and np.abs(F - want[1]).max() < 1e-5
+
+
+CASES = {f.__name__: f for f in (pointers_not_sent, pageable_after_one, pageable_after_two, no_copies_at_all)}
 
 
 @pytest.fixture(scope="module")
