@@ -10,7 +10,7 @@ Conventions (shared with the library's public header):
 """
 from __future__ import annotations
 
-from dataclasses import dataclass, field
+from dataclasses import dataclass, field, replace
 
 import numpy as np
 
@@ -435,13 +435,15 @@ def colour_frames(stream: Stream, frames=None, seed: int = 17) -> np.ndarray:
 def make_stream(name: str, n_frames: int | None = None, seed: int | None = None,
                 noise: bool = True, cache: bool = True) -> Stream:
     """Seeded synthetic stream for a named workload ("tiny", "vga", "large", "room").
-    `noise=False` gives exact depth (used by the closed-form checks)."""
+    `noise=False` gives exact depth (used by the closed-form checks).  Every call
+    returns a stream of its own (what is set on one is not seen on another) over the
+    rendered arrays, which the calls share."""
     p = workload_params(name)
     seed = p["seed"] if seed is None else seed
     n = p["n_frames"] if n_frames is None else n_frames
     key = (name, n, seed, noise)
     if cache and key in _STREAM_CACHE:
-        return _STREAM_CACHE[key]
+        return _own(_STREAM_CACHE[key])
     rng = np.random.default_rng(seed)
     K = (p["fx"], p["fy"], p["cx"], p["cy"])
     W, H = p["width"], p["height"]
@@ -475,4 +477,8 @@ def make_stream(name: str, n_frames: int | None = None, seed: int | None = None,
                 scene=scene, seed=seed, noise=noise)
     if cache:
         _STREAM_CACHE[key] = st
-    return st
+    return _own(st)
+
+
+def _own(st: Stream) -> Stream:
+    return replace(st, params=dict(st.params))
