@@ -171,8 +171,10 @@ itm_status itm_expected_depths(itm_scene *scene, const itm_intrinsics *K, const 
  *   capacity  blocks the buffers hold; ITM_ERR_ARG when smaller than the count
  *   n_blocks  HOST int64 out: number of allocated blocks
  * The first export of voxels or colour allocates 32 MiB of staging on the device
- * and 32 MiB pinned on the host, kept by the scene; up to 8 host threads fill the
- * buffers during the call.  Synchronises the stream. */
+ * and 32 MiB pinned on the host, kept by the scene, and goes without either where
+ * there is no room for it; up to 8 host threads fill the buffers during the call.
+ * Every call takes 40 bytes per block, on the device or, where none is left,
+ * pinned, and gives them back.  Synchronises the stream. */
 itm_status itm_export_blocks(itm_scene *scene, int32_t *coords, float *sdf, float *w,
                              int64_t capacity, int64_t *n_blocks);
 
@@ -188,9 +190,12 @@ itm_status itm_export_blocks(itm_scene *scene, int32_t *coords, float *sdf, floa
  *   sdf, w  HOST float[n * 512] each, export layout; F in [-1, 1], W an
  *           integer in [0, max_w]
  * ITM_ERR_ARG for NULL buffers, repeated keys or values out of range (nothing
- * is changed then).  From 48 MiB on the arrays go through the export's pinned
- * staging, filled by at most 8 threads that end with the call.  Synchronises the
- * stream. */
+ * is changed then).  The call takes 40 bytes per block and, for a map of up to
+ * 1 GiB (262,144 blocks), its voxels' size, on the device; a larger map, or one
+ * that finds no such room, goes over twice, 64 MiB at a time (pinned where the
+ * device has no room for that either).  From 48 MiB on the arrays go through the
+ * export's pinned staging, filled by at most 8 threads that end with the call.
+ * Synchronises the stream. */
 itm_status itm_import_blocks(itm_scene *scene, const int32_t *coords, const float *sdf, const float *w,
                              int64_t n);
 

@@ -80,10 +80,11 @@ static_assert(sizeof(Excess) == 16, "excess record is 16 bytes");
 struct Counters {
     int32_t vba_next;       // voxel blocks allocated (a count: block = entry id)
     int32_t excess_next;    // excess entries handed out (may run past n_excess)
-    int32_t pad0;
+    int32_t collected;      // of an export: keys collected
     int32_t set_used[3];    // claim-set slots used, by frame % 3
     unsigned long long dropped_total;
-    unsigned long long pad2[5];
+    unsigned long long import_bad;   // of an import: its first voxel that is no valid state
+    unsigned long long pad2[4];
     // counts striped over separate 128-byte lines so that the per-workgroup
     // additions do not all hit one address: [frame parity][stripe] for a frame,
     // [2][stripe] since creation.  A frame's kernel adds to its parity's counters

@@ -1003,13 +1003,31 @@ namespace {
 
 struct BlockRec { int32_t x, y, z, blk; };
 
-// device memory of one call, freed at its end
-struct DevMem {
+// Memory of one call, freed at its end: the device's, or, where none is left,
+// pinned memory, which kernels read and write over the link (but no atomics).
+struct CallMem {
     void *p = nullptr;
-    DevMem() = default;
-    DevMem(const DevMem &) = delete;
-    DevMem &operator=(const DevMem &) = delete;
-    ~DevMem() { (void)hipFree(p); }
+    bool pinned = false;
+    CallMem() = default;
+    CallMem(const CallMem &) = delete;
+    CallMem &operator=(const CallMem &) = delete;
+    ~CallMem() { (void)(pinned ? hipHostFree(p) : hipFree(p)); }
+    bool device(size_t bytes)
+    {
+        if (hipMalloc(&p, bytes) == hipSuccess) return true;
+        p = nullptr;
+        (void)hipGetLastError();
+        return false;
+    }
+    itm_status any(size_t bytes, const char *what)
+    {
+        if (device(bytes)) return ITM_OK;
+        pinned = hipHostMalloc(&p, bytes) == hipSuccess;
+        if (pinned) return ITM_OK;
+        p = nullptr;
+        (void)hipGetLastError();
+        return fail(ITM_ERR_OOM, "allocating %zu bytes for %s", bytes, what);
+    }
 };
 
 // entries holding a key (synchronises the stream)
@@ -1022,18 +1040,18 @@ itm_status allocated_blocks(itm_scene *sc, int64_t *n)
     return ITM_OK;
 }
 
-// the n allocated blocks (key and entry) in key order (x, y, z), on the device.
+// the n allocated blocks (key and entry) in key order (x, y, z), in the device's reach.
 // Asynchronous.
-itm_status sorted_blocks(itm_scene *sc, int64_t n, DevMem &mem, SortedBlocks *b)
+itm_status sorted_blocks(itm_scene *sc, int64_t n, CallMem &mem, SortedBlocks *b)
 {
-    if (itm_status st = dev_alloc(&mem.p, 40 * (size_t)n + 16, "export list")) return st;
+    if (itm_status st = mem.any(40 * (size_t)n, "export list")) return st;
     b->key = (unsigned long long *)mem.p;
     b->key2 = b->key + n;
     b->ent = (int32_t *)(b->key2 + n);
     b->ent2 = b->ent + n;
     b->out_ent = b->ent2 + n;
     b->coords = b->out_ent + n;
-    b->count = b->coords + 3 * n;
+    b->count = &sc->cnt->collected;
     HIP_TRY(launch_sort_blocks(hash_view(sc), (int32_t)n, *b, sc->stream));
     return ITM_OK;
 }
@@ -1045,12 +1063,12 @@ itm_status collect_blocks(itm_scene *sc, std::vector<BlockRec> &recs)
     if (itm_status st = allocated_blocks(sc, &n)) return st;
     recs.resize(n);
     if (n == 0) return ITM_OK;
-    DevMem mem;
+    CallMem mem;
     SortedBlocks b;
     if (itm_status st = sorted_blocks(sc, n, mem, &b)) return st;
     std::vector<int32_t> ent(n), xyz(3 * n);
-    HIP_TRY(hipMemcpyAsync(ent.data(), b.out_ent, sizeof(int32_t) * n, hipMemcpyDeviceToHost, sc->stream));
-    HIP_TRY(hipMemcpyAsync(xyz.data(), b.coords, sizeof(int32_t) * 3 * n, hipMemcpyDeviceToHost, sc->stream));
+    HIP_TRY(hipMemcpyAsync(ent.data(), b.out_ent, sizeof(int32_t) * n, hipMemcpyDefault, sc->stream));
+    HIP_TRY(hipMemcpyAsync(xyz.data(), b.coords, sizeof(int32_t) * 3 * n, hipMemcpyDefault, sc->stream));
     HIP_TRY(hipStreamSynchronize(sc->stream));
     for (int64_t i = 0; i < n; i++) recs[i] = BlockRec{xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], ent[i]};
     return ITM_OK;
@@ -1061,8 +1079,7 @@ itm_status collect_blocks(itm_scene *sc, std::vector<BlockRec> &recs)
 // ---------------------------------------------------------------------------
 constexpr size_t kStageBytes = size_t(16) << 20;   // a slot: 4096 blocks of F and W
 
-// one destination array: bytes per block, in block order
-// one array of the caller's, bytes per block
+// one array of the caller's: bytes per block, in block order
 struct HostPart {
     uint8_t *p;
     size_t bytes;
@@ -1194,19 +1211,25 @@ template <typename Fill>
 itm_status stream_out(itm_scene *sc, int64_t n, const HostPart *parts, int n_parts, Fill fill)
 {
     if (itm_status st = ensure_slots(sc)) return st;
-    if (!sc->stage_dev)
-        if (itm_status st = dev_alloc((void **)&sc->stage_dev, 2 * kStageBytes, "export staging")) return st;
-    if (!sc->stage_host) {
+    if (!sc->stage_dev && hipMalloc((void **)&sc->stage_dev, 2 * kStageBytes) != hipSuccess) {
+        sc->stage_dev = nullptr;
+        (void)hipGetLastError();
+    }
+    if (!sc->stage_host || !sc->stage_dev) {   // no room for the staging: chunk by chunk, copied by the runtime
         size_t per = 0;
         for (int k = 0; k < n_parts; k++) per += parts[k].bytes;
-        const int64_t chunk = (int64_t)(kStageBytes / per);
+        const int64_t chunk = std::min(n, (int64_t)(kStageBytes / per));
+        CallMem mem;
+        if (!sc->stage_dev)
+            if (itm_status st = mem.any(per * (size_t)chunk, "export chunk")) return st;
+        uint8_t *dev = sc->stage_dev ? sc->stage_dev : (uint8_t *)mem.p;
         for (int64_t off = 0; off < n; off += chunk) {
             const int64_t m = std::min(chunk, n - off);
-            const uint8_t *src = sc->stage_dev;
-            HIP_TRY(fill(off, m, sc->stage_dev));
+            const uint8_t *src = dev;
+            HIP_TRY(fill(off, m, dev));
             for (int k = 0; k < n_parts; k++) {
                 HIP_TRY(hipMemcpyAsync(parts[k].p + parts[k].bytes * (size_t)off, src, parts[k].bytes * (size_t)m,
-                                       hipMemcpyDeviceToHost, sc->stream));
+                                       hipMemcpyDefault, sc->stream));
                 src += parts[k].bytes * (size_t)m;
             }
             HIP_TRY(hipStreamSynchronize(sc->stream));
@@ -1250,7 +1273,7 @@ hipError_t stream_in(itm_scene *sc, int64_t n, const HostPart *parts, int n_part
     if (per * (size_t)n < 3 * kStageBytes || ensure_slots(sc) != ITM_OK || !sc->stage_host) {
         hipError_t e = hipSuccess;
         for (int k = 0; k < n_parts && e == hipSuccess; k++)
-            e = hipMemcpyAsync(dst[k], parts[k].p, parts[k].bytes * (size_t)n, hipMemcpyHostToDevice, sc->stream);
+            e = hipMemcpyAsync(dst[k], parts[k].p, parts[k].bytes * (size_t)n, hipMemcpyDefault, sc->stream);
         return e;
     }
     SlotCopier cp(sc->stage_host, parts, n_parts, n, false);
@@ -1267,7 +1290,7 @@ hipError_t stream_in(itm_scene *sc, int64_t n, const HostPart *parts, int n_part
             const uint8_t *src = cp.slot(p);
             for (int k = 0; k < n_parts && e == hipSuccess; k++) {
                 const size_t bytes = parts[k].bytes * (size_t)cp.size(p);
-                e = hipMemcpyAsync(dst[k] + parts[k].bytes * (size_t)cp.first(p), src, bytes, hipMemcpyHostToDevice,
+                e = hipMemcpyAsync(dst[k] + parts[k].bytes * (size_t)cp.first(p), src, bytes, hipMemcpyDefault,
                                    sc->stream);
                 src += bytes;
             }
@@ -1291,11 +1314,11 @@ itm_status itm_export_blocks(itm_scene *sc, int32_t *coords, float *sdf, float *
     if (!coords && !sdf && !w) return ITM_OK;
     if (capacity < n) return fail(ITM_ERR_ARG, "capacity %lld < %lld blocks", (long long)capacity, (long long)n);
     if (n == 0) return ITM_OK;
-    DevMem mem;
+    CallMem mem;
     SortedBlocks b;
     if (itm_status st = sorted_blocks(sc, n, mem, &b)) return st;
     if (coords)
-        HIP_TRY(hipMemcpyAsync(coords, b.coords, sizeof(int32_t) * 3 * n, hipMemcpyDeviceToHost, sc->stream));
+        HIP_TRY(hipMemcpyAsync(coords, b.coords, sizeof(int32_t) * 3 * n, hipMemcpyDefault, sc->stream));
     if (!sdf && !w) {
         HIP_TRY(hipStreamSynchronize(sc->stream));
         return ITM_OK;
@@ -1315,7 +1338,7 @@ itm_status itm_export_blocks(itm_scene *sc, int32_t *coords, float *sdf, float *
     // (a host copy not merged yet: exported merged, as the swap-in would merge it)
     std::vector<int32_t> ent(n), dblk(sc->n_entries), slots(sc->n_entries);
     std::vector<uint8_t> onh(sc->n_entries);
-    HIP_TRY(hipMemcpyAsync(ent.data(), b.out_ent, sizeof(int32_t) * n, hipMemcpyDeviceToHost, sc->stream));
+    HIP_TRY(hipMemcpyAsync(ent.data(), b.out_ent, sizeof(int32_t) * n, hipMemcpyDefault, sc->stream));
     HIP_TRY(hipMemcpyAsync(dblk.data(), sc->blk, sizeof(int32_t) * sc->n_entries, hipMemcpyDeviceToHost,
                            sc->stream));
     HIP_TRY(hipMemcpyAsync(onh.data(), sc->onhost, sc->n_entries, hipMemcpyDeviceToHost, sc->stream));
@@ -1481,22 +1504,18 @@ itm_status itm_import_blocks(itm_scene *sc, const int32_t *coords, const float *
     constexpr int64_t kStageAll = int64_t(1) << 30, kChunk = 16384;   // a chunk: 32 MiB per array
     const size_t blk_bytes = sizeof(float) * kBlockVox;
     const int64_t n1 = std::max<int64_t>(n, 1);
-    DevMem vox, keys;
-    bool whole = n1 * 2 * (int64_t)blk_bytes <= kStageAll;
-    if (whole && hipMalloc(&vox.p, 2 * blk_bytes * n1) != hipSuccess) {
-        vox.p = nullptr;
-        (void)hipGetLastError();
-        whole = false;
-    }
+    // The lists first: they are needed, the whole map's place is not.
+    CallMem keys, vox;
+    if (itm_status st = keys.any(40 * (size_t)n1 + 8, "import keys")) return st;
+    const bool whole = n1 * 2 * (int64_t)blk_bytes <= kStageAll && vox.device(2 * blk_bytes * n1);
     const int64_t chunk = whole ? n1 : std::min(n1, kChunk);
     if (!whole)
-        if (itm_status st = dev_alloc(&vox.p, 2 * blk_bytes * chunk, "import voxels")) return st;
+        if (itm_status st = vox.any(2 * blk_bytes * chunk, "import voxels")) return st;
     float *d_s = (float *)vox.p, *d_w = d_s + kBlockVox * chunk;
-    // first bad voxel, sort scratch, coordinates, entries, the repeat flag
-    if (itm_status st = dev_alloc(&keys.p, 16 + 40 * (size_t)n1, "import keys")) return st;
-    unsigned long long *d_first = (unsigned long long *)keys.p;
+    unsigned long long *d_first = &sc->cnt->import_bad;
+    // sort scratch, coordinates, entries, the repeat flag
     SortedBlocks sb = {};
-    sb.key = d_first + 1;
+    sb.key = (unsigned long long *)keys.p;
     sb.key2 = sb.key + n1;
     sb.ent = (int32_t *)(sb.key2 + n1);
     sb.ent2 = sb.ent + n1;
@@ -1516,7 +1535,7 @@ itm_status itm_import_blocks(itm_scene *sc, const int32_t *coords, const float *
         int32_t dup = 0;
         e = hipMemcpyAsync(d_first, &first, sizeof first, hipMemcpyHostToDevice, sc->stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(d_coords, coords, sizeof(int32_t) * 3 * n, hipMemcpyHostToDevice, sc->stream);
+            e = hipMemcpyAsync(d_coords, coords, sizeof(int32_t) * 3 * n, hipMemcpyDefault, sc->stream);
         if (e == hipSuccess) e = launch_find_repeats(d_coords, (int32_t)n, sb, d_dup, sc->stream);
         for (int64_t off = 0; off < n && e == hipSuccess; off += chunk) {
             const int64_t m = std::min(chunk, n - off);
@@ -1526,7 +1545,7 @@ itm_status itm_import_blocks(itm_scene *sc, const int32_t *coords, const float *
             if (e == hipSuccess && !whole) e = hipStreamSynchronize(sc->stream);   // the chunk's memory is used again
         }
         if (e == hipSuccess) e = hipMemcpyAsync(&first, d_first, sizeof first, hipMemcpyDeviceToHost, sc->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(&dup, d_dup, sizeof dup, hipMemcpyDeviceToHost, sc->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(&dup, d_dup, sizeof dup, hipMemcpyDefault, sc->stream);
         const hipError_t es = hipStreamSynchronize(sc->stream);   // also before the memory above is freed
         if (e == hipSuccess) e = es;
         if (e != hipSuccess) return fail(ITM_ERR_HIP, "import failed: %s", hipGetErrorString(e));
@@ -1563,7 +1582,7 @@ itm_status itm_export_colour(itm_scene *sc, uint8_t *rgbw, int64_t capacity, int
     *n_blocks = n;
     if (!rgbw || n == 0) return ITM_OK;
     if (capacity < n) return fail(ITM_ERR_ARG, "capacity %lld < %lld blocks", (long long)capacity, (long long)n);
-    DevMem mem;
+    CallMem mem;
     SortedBlocks b;
     if (itm_status st = sorted_blocks(sc, n, mem, &b)) return st;
     const HostPart part{rgbw, sizeof(uchar4) * kBlockVox};

@@ -100,7 +100,76 @@ def no_copies_at_all(itm, torch, hip, st):
     assert np.array_equal(c, want[0]) and np.array_equal(W, want[2]) and np.abs(F - want[1]).max() < 1e-5
 
 
-CASES = {f.__name__: f for f in (pointers_not_sent, pageable_after_one, pageable_after_two, no_copies_at_all)}
+def _map(n):
+    rng = np.random.default_rng(n)
+    c = np.unique(rng.integers(-60, 60, (2 * n, 3)), axis=0)
+    c = c[rng.permutation(len(c))[:n]].astype(np.int32)
+    F = (rng.integers(-32767, 32768, (n, 512)) / 32767).astype(np.float32)
+    return c, F, rng.integers(0, 101, (n, 512)).astype(np.float32)
+
+
+def _in_and_out(itm, n, limits):
+    """A map of n blocks imported and exported, each call under limits(): refused as ever
+    where it has to be, and the same map."""
+    c, F, W = _map(n)
+    at = np.lexsort((c[:, 2], c[:, 1], c[:, 0]))
+    sc = itm.Scene(0.005, 0.02, 100, 1 << 15, 1 << 13)
+    sc.enable_colour()
+    for change, match in (((c[n - 1], c[0]), "twice"), ((F, 7 * 512 + 3), f"voxel {7 * 512 + 3}: F"),
+                          ((W, n * 512 - 1), f"voxel {n * 512 - 1}: W")):
+        a, b = change
+        if match == "twice":
+            old = a.copy()
+            a[:] = b
+        else:
+            old = a.reshape(-1)[b]
+            a.reshape(-1)[b] = -1.5
+        limits()
+        try:
+            sc.import_blocks(c, F, W)
+            raise AssertionError(match)
+        except itm.ItmError as e:
+            assert match in str(e), e
+        if match == "twice":
+            a[:] = old
+        else:
+            a.reshape(-1)[b] = old
+    assert sc.stats()["n_allocated"] == 0
+    limits()
+    sc.import_blocks(c, F, W)
+    limits()
+    got = sc.export()
+    limits()
+    only = sc.export(values=False)[0]
+    limits()
+    rgbw = sc.export_colour()
+    sc.close()
+    assert np.array_equal(got[0], c[at]) and np.array_equal(only, c[at])
+    assert np.array_equal(got[1], F[at]) and np.array_equal(got[2], W[at])
+    assert rgbw.shape == (n, 512, 4) and not rgbw.any()
+
+
+def device_memory_for_one(itm, torch, hip, st):
+    """Device memory for one list, or one larger allocation, a call: the lists, which a
+    call cannot do without, come before what only makes it faster."""
+    _in_and_out(itm, 16389, lambda: hip.limit_device(40 * 16389, 1))
+    assert hip.refusals() > 0
+
+
+def no_device_memory(itm, torch, hip, st):
+    """No device memory at all beside the scene's: lists, voxels and staging are pinned."""
+    _in_and_out(itm, 5000, lambda: hip.limit_device(0, 0))
+    assert hip.refusals() > 0
+
+
+def no_staging(itm, torch, hip, st):
+    """No pinned memory: the runtime copies to and from the caller's arrays."""
+    _in_and_out(itm, 16389, lambda: hip.limit_host(0, 0))
+    assert hip.refusals() > 0
+
+
+CASES = {f.__name__: f for f in (pointers_not_sent, pageable_after_one, pageable_after_two, no_copies_at_all,
+                                 device_memory_for_one, no_device_memory, no_staging)}
 
 
 @pytest.fixture(scope="module")
