@@ -406,27 +406,37 @@ __global__ __launch_bounds__(256) void k_alloc(FuseArgs a)
     }
 }
 
-// The order of the raycast's tiles, fullest bins first, by one workgroup of the
-// integration (the allocation has filled the bins; nothing here waits for it).  A
-// raycast's launch ends with its longest marches, and those are in tiles that see
-// many blocks: started first, they end with the rest.  The counts are sorted in 256
-// classes of two; tiles of a class come in any order.
-// k_raycast: 1280x720 F16 (3600 tiles) 122.4 -> 104.3 us, 640x480 F32 (1200) 51.1 ->
-// 48.2 (classes of 16: 107.0 and 47.8).  The order is used from 3 tiles per CU on: a frame of 592x432
-// (999 tiles) takes 76.3 us against 78.0 without it, of 560x400 (875) and 480x360
-// (690) the same, of 400x300 (475) 75.2 against 74.2 -- all of its workgroups are
-// resident at once and the bands share their XCD's L2 (in order a VGA raycast reads 24 MB
-// from memory, in bands 15).  Up to 65536 tiles, which
-// one workgroup sorts in less than the integration of such a frame takes.
-__device__ __forceinline__ void order_tiles(const RangeBins &rb)
+// The order of the raycast's tiles, fullest bins first, by the first kOrderWgs
+// workgroups of the integration (the allocation has filled the bins; nothing here
+// waits for it).  A raycast's launch ends with its longest marches, and those are in
+// tiles that see many blocks: started first, they end with the rest.  Workgroup x
+// sorts the tiles x, x + 8, ... into the places x, x + 8, ...: neighbours differ
+// little, so the eight lists run down together.  The counts are sorted in 256 classes
+// of two; tiles of a class come in any order.
+//
+// k_raycast: 1280x720 F16 at 4 mm (3600 tiles) 122 -> 100 us, 640x480 F32 at 5 mm
+// (1200) 50.5 -> 46.6, 3840x2160 F16 at 8 mm (32400) 588 -> 518.  The order is used
+// from 3 tiles per CU on: a frame of 592x432 (999 tiles) takes 76.3 us against 78.0
+// without it, of 560x400 (875) and 480x360 (690) the same, of 400x300 (475) 75.2
+// against 74.2 -- all of its workgroups are resident at once and the bands share
+// their XCD's L2.  A raycast that finds nothing pays for reading its places (VGA 5.0
+// -> 6.2 us).
+//
+// The sort is two rounds of reads and of LDS counting, and has to be over when the
+// integration is, which for a frame that sees little takes 4 us.  By one workgroup it
+// took 8.6 us at 3600 tiles, 27 at 14400 and 111 at 65536 (tiles that see nothing are
+// one class and queue at its count); by eight 4.0, 6.0 and 18.
+constexpr int kOrderWgs = 8;
+__device__ __forceinline__ void order_tiles(const RangeBins &rb, int x)
 {
     __shared__ int32_t s_at[256], s_wave[4];
-    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave, n = rb.tw * rb.th;
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+    const int n = (rb.tw * rb.th - x + kOrderWgs - 1) / kOrderWgs;   // tiles x, x + kOrderWgs, ...
     auto each = [&](auto use) {   // 8 counts in flight
         for (int i0 = t; i0 < n; i0 += 8 * 256) {
             int32_t c[8];
 #pragma unroll
-            for (int k = 0; k < 8; k++) c[k] = rb.cnt[min(i0 + 256 * k, n - 1)];
+            for (int k = 0; k < 8; k++) c[k] = rb.cnt[x + kOrderWgs * min(i0 + 256 * k, n - 1)];
 #pragma unroll
             for (int k = 0; k < 8; k++)
                 if (i0 + 256 * k < n) use(i0 + 256 * k, 255 - min(c[k] >> 1, 255));
@@ -448,7 +458,7 @@ __device__ __forceinline__ void order_tiles(const RangeBins &rb)
     for (int w = 0; w < wave; w++) incl += s_wave[w];
     s_at[t] = incl - c;
     __syncthreads();
-    each([&](int i, int cls) { rb.order[atomicAdd(&s_at[cls], 1)] = i; });
+    each([&](int i, int cls) { rb.order[x + kOrderWgs * atomicAdd(&s_at[cls], 1)] = x + kOrderWgs * i; });
 }
 
 // Integration.  Wave gw (pair of waves with colour) begins with place gw / 32 of
@@ -470,9 +480,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CLR ? 6 : 5
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     uint32_t n_upd = 0, n_blk = 0;
     constexpr int kP = kParts<CLR>;
-    constexpr int skip = ORD ? 1 : 0;   // workgroup 0 puts the raycast's tiles in order
-    if (ORD && blockIdx.x == 0) {
-        order_tiles(a.rb);
+    constexpr int skip = ORD ? kOrderWgs : 0;   // workgroups that put the raycast's tiles in order
+    if (ORD && blockIdx.x < skip) {
+        order_tiles(a.rb, blockIdx.x);
         return;
     }
     const int gw = (((int)blockIdx.x - skip) * 4 + wave) / kP, nw = ((int)gridDim.x - skip) * 4 / kP;

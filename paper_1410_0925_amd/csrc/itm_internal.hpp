@@ -289,7 +289,7 @@ struct alignas(16) RangeRect {
 static_assert(sizeof(RangeRect) == 16, "range rectangle is 16 bytes");
 constexpr int kTile = 16;
 
-constexpr int64_t kMaxOrdered = 1 << 16;   // tiles that one workgroup puts in order
+constexpr int64_t kMaxOrdered = 1 << 16;   // tiles that the integration puts in order (itm_integrate.hip)
 struct RangeBins {
     int32_t *cnt;         // [n_tiles] rectangles appended (may exceed cap)
     RangeRect *rect;      // [n_tiles][cap]

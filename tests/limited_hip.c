@@ -1,13 +1,17 @@
 /* The HIP calls through which the library takes memory and sends it pointers, with limits
  * that a test sets: loaded before everything else, these come first in the lookup of
  * their names and pass on to the runtime what the limits allow.  A refused call changes
- * nothing and returns the runtime's own error code. */
+ * nothing and returns the runtime's own error code.  Kernel launches are passed on and
+ * those of a name counted. */
 #define _GNU_SOURCE
 #include <dlfcn.h>
 #include <stddef.h>
+#include <string.h>
 
 typedef int (*malloc_t)(void **, size_t);
 typedef int (*host_malloc_t)(void **, size_t, unsigned);
+typedef struct { unsigned x, y, z; } dim3_t;
+typedef int (*launch_t)(const void *, dim3_t, dim3_t, void **, size_t, void *);
 typedef int (*copy_t)(void *, const void *, size_t, int, void *);
 
 /* hipErrorOutOfMemory, hipErrorUnknown, hipMemcpyHostToDevice */
@@ -51,4 +55,24 @@ int hipMemcpyAsync(void *dst, const void *src, size_t n, int kind, void *stream)
 {
     if (kind == kHostToDevice && n <= copy_to && copy_left > 0) return copy_left--, refused++, kUnknown;
     return ((copy_t)runtime("hipMemcpyAsync"))(dst, src, n, kind, stream);
+}
+
+static char counted[128];
+static long launches;
+
+/* launches since last asked of kernels whose (mangled) name holds the one given then;
+ * from here on those of `name` */
+long launches_of(const char *name)
+{
+    long n = launches;
+    launches = 0;
+    strncpy(counted, name, sizeof counted - 1);
+    return n;
+}
+
+int hipLaunchKernel(const void *f, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream)
+{
+    Dl_info at;
+    if (counted[0] && dladdr(f, &at) && at.dli_sname && strstr(at.dli_sname, counted)) launches++;
+    return ((launch_t)runtime("hipLaunchKernel"))(f, grid, block, args, lds, stream);
 }

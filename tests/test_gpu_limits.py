@@ -1,6 +1,7 @@
-"""What the library does where memory or a transfer is refused.  The refusals are made
-on the host, by limited_hip.c in front of the HIP runtime, in one process of their own
-(this file, run as a program); every kernel runs to its normal end."""
+"""What the library does where memory or a transfer is refused, and which kernel a rule
+picks.  The refusals are made, and the launches counted, on the host, by limited_hip.c
+in front of the HIP runtime, in one process of their own (this file, run as a program);
+every kernel runs to its normal end."""
 import ctypes as C
 import json
 import os
@@ -168,8 +169,44 @@ def no_staging(itm, torch, hip, st):
     assert hip.refusals() > 0
 
 
+def tiles_in_order(itm, torch, hip, st):
+    """A raycast at the frame's own pose takes its tiles in the integration's order from 3
+    tiles per compute unit on, up to 65536, and in bands beside that range; at the same
+    pose with a zero of the other sign always in bands.  The rays are the same bit for
+    bit, and every tile is cast (the outputs are NaN before)."""
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cu % 8 == 0
+    ordered = b"k_raycastILi0ELb0ELb0ELb1EEE"
+    sizes = [((cu // 8) * 16, 24 * 16 - 16, False), ((cu // 8) * 16, 24 * 16, True),
+             ((cu // 8) * 16 + 1, 24 * 16 + 3, True), (4096, 4096, True), (4097, 4096, False)]
+    T, other = np.eye(4), np.eye(4)
+    other[3, 0] = -0.0
+    for w, h, order in sizes:
+        print(f"  {w}x{h}", flush=True)
+        K = (0.8 * w, 0.8 * w, (w - 1) / 2, (h - 1) / 2, w, h)
+        depth = torch.full((h, w), 1.5, device="cuda")
+        depth += 0.3 * (torch.arange(w, device="cuda") / w > 0.6)
+        depth[:, : w // 3] = 0.0                         # tiles that see nothing
+        sc = itm.Scene(0.02, 0.08, 100, 1 << 15, 1 << 13)
+        sc.set_search_range(True)
+        sc.integrate(depth, K, T)
+        rays = []
+        for pose in (T, other):
+            out = [torch.full((h, w, 4), float("nan"), device="cuda") for _ in range(2)]
+            hip.launches_of(ordered)
+            sc.raycast(K, pose, *out)
+            n = hip.launches_of(b"")
+            assert n == (1 if order and pose is T else 0), (w, h, n)
+            rays.append(out)
+        for a, b in zip(*rays):
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+        P = rays[0][0]
+        assert not P.isnan().any() and 0.3 < (P[..., 3] > 0).float().mean() < 0.9
+        sc.close()
+
+
 CASES = {f.__name__: f for f in (pointers_not_sent, pageable_after_one, pageable_after_two, no_copies_at_all,
-                                 device_memory_for_one, no_device_memory, no_staging)}
+                                 device_memory_for_one, no_device_memory, no_staging, tiles_in_order)}
 
 
 @pytest.fixture(scope="module")
@@ -194,7 +231,8 @@ if __name__ == "__main__":
     hip = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)     # before the runtime is loaded
     for name in ("limit_host", "limit_device", "fail_copies"):
         getattr(hip, name).argtypes = [C.c_size_t, C.c_long]
-    hip.refusals.restype = C.c_long
+    hip.launches_of.argtypes = [C.c_char_p]
+    hip.refusals.restype = hip.launches_of.restype = C.c_long
     sys.path.insert(0, ROOT)
     import traceback
 
