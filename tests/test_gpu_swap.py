@@ -152,3 +152,20 @@ def test_blocks_that_merge_and_leave_in_one_frame(fmt, swap_in, swap_out, stride
            "s16u8": lambda W: (0.5 / 32767 + 4 * 2.0 ** -23) * (np.asarray(W, np.float64) + 1) + 1e-6}[fmt]
     compare_volumes(g.export(), o.export(), tol=tol, cands=o.export_candidates())
     g.close()
+
+
+def test_slots_go_round():
+    """More blocks swapped in than the table has entries, so that the ring of free host
+    slots starts over: numbers moved per frame and volume as above."""
+    itm, torch = gpu()
+    st = make_stream("tiny", n_frames=60)
+    order = [(13 * k) % 60 for k in range(60)]
+    st.depth, st.T_wc = st.depth[order], st.T_wc[order]
+    st.params = dict(voxel_size=0.025, mu=0.1, max_w=100, n_buckets=2 ** 8, n_excess=131)
+    print("case: tiny, 643 entries, transfers of 40 and 60 blocks", flush=True)
+    g, o, _ = run_both(st, 60, 500, 40, 60)
+    s = g.stats()
+    assert s["n_entries"] == 643 and g.swap_stats()["swapped_in_total"] > 643
+    assert o.stats()["n_dropped_total"] == 0
+    compare_volumes(g.export(), o.export(), cands=o.export_candidates())
+    g.close()
