@@ -170,10 +170,11 @@ itm_status itm_expected_depths(itm_scene *scene, const itm_intrinsics *K, const 
  *           W as a float, voxel order lx + 8 ly + 64 lz
  *   capacity  blocks the buffers hold; ITM_ERR_ARG when smaller than the count
  *   n_blocks  HOST int64 out: number of allocated blocks
- * The first export of voxels or colour allocates 32 MiB of staging on the device
- * and 32 MiB pinned on the host, kept by the scene, and goes without either where
- * there is no room for it; up to 8 host threads fill the buffers during the call.
- * Every call takes 40 bytes per block, on the device or, where none is left,
+ * The first export of 48 MiB of voxels or colour (the second of 16 MiB) allocates
+ * 32 MiB of staging on the device and 32 MiB pinned on the host, kept by the scene,
+ * where there is room for it; exports that use it start up to 8 host threads, which
+ * fill the buffers and end with the call.  Every call takes 40 bytes per block and,
+ * without the staging, up to 16 MiB for voxels, on the device or, where none is left,
  * pinned, and gives them back.  Synchronises the stream. */
 itm_status itm_export_blocks(itm_scene *scene, int32_t *coords, float *sdf, float *w,
                              int64_t capacity, int64_t *n_blocks);
@@ -193,9 +194,9 @@ itm_status itm_export_blocks(itm_scene *scene, int32_t *coords, float *sdf, floa
  * is changed then).  The call takes 40 bytes per block and, for a map of up to
  * 1 GiB (262,144 blocks), its voxels' size, on the device; a larger map, or one
  * that finds no such room, goes over twice, 64 MiB at a time (pinned where the
- * device has no room for that either).  From 48 MiB on the arrays go through the
- * export's pinned staging, filled by at most 8 threads that end with the call.
- * Synchronises the stream. */
+ * device has no room for that either).  A scene's first import from 96 MiB on,
+ * later ones from 48 MiB on, go through the export's pinned staging, filled by at
+ * most 8 threads that end with the call.  Synchronises the stream. */
 itm_status itm_import_blocks(itm_scene *scene, const int32_t *coords, const float *sdf, const float *w,
                              int64_t n);
 

@@ -159,21 +159,23 @@ __global__ __launch_bounds__(256) void k_coord_keys(const int32_t *coords, int32
 }
 
 // sort each tile of kSortTile keys (with their entries) in LDS: a bitonic network,
-// the last tile padded with keys above all
+// the last tile padded with keys above all to a power of two (a few keys take 3 us,
+// all 4096 places 25)
 __global__ __launch_bounds__(1024) void k_sort_tiles(unsigned long long *key, int32_t *ent, int32_t n)
 {
     __shared__ unsigned long long s_k[kSortTile];
     __shared__ int32_t s_e[kSortTile];
     const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int i = threadIdx.x; i < kSortTile; i += 1024) {
+    const int m = (int)min(n - base, (int64_t)kSortTile), size = m < 2 ? 1 : 2 << (31 - __clz(m - 1));
+    for (int i = threadIdx.x; i < size; i += 1024) {
         const bool in = base + i < n;
         s_k[i] = in ? key[base + i] : ~0ull;
         s_e[i] = in ? ent[base + i] : -1;
     }
-    for (int k = 2; k <= kSortTile; k <<= 1)
+    for (int k = 2; k <= size; k <<= 1)
         for (int j = k >> 1; j > 0; j >>= 1) {
             __syncthreads();
-            for (int i = threadIdx.x; i < kSortTile / 2; i += 1024) {
+            for (int i = threadIdx.x; i < size / 2; i += 1024) {
                 const int a = ((i & ~(j - 1)) << 1) | (i & (j - 1)), b = a | j;
                 const unsigned long long ka = s_k[a], kb = s_k[b];
                 if ((ka > kb) == ((a & k) == 0)) {
@@ -186,11 +188,10 @@ __global__ __launch_bounds__(1024) void k_sort_tiles(unsigned long long *key, in
             }
         }
     __syncthreads();
-    for (int i = threadIdx.x; i < kSortTile; i += 1024)
-        if (base + i < n) {
-            key[base + i] = s_k[i];
-            ent[base + i] = s_e[i];
-        }
+    for (int i = threadIdx.x; i < m; i += 1024) {
+        key[base + i] = s_k[i];
+        ent[base + i] = s_e[i];
+    }
 }
 
 // Merge the sorted runs of `run` keys pairwise: a key's place in the merged run is

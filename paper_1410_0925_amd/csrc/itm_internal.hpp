@@ -488,6 +488,7 @@ struct SortedBlocks {
     int32_t *out_ent;                 // [n] entries in key order
     int32_t *coords;                  // [n][3] (x, y, z) in key order
     int32_t *count;                   // keys collected
+    uint8_t *extra;                   // 256-byte aligned memory behind the lists, for the caller
 };
 constexpr int kSortTile = 4096;
 // the table's n keys: out_ent and coords

@@ -113,8 +113,9 @@ struct itm_scene {
     uchar4 *clr = nullptr;            // [vba_cap][512] colour voxels, allocated on enable
 
     // staging of the exports and of large imports, two slots of kStageBytes pinned on
-    // the host and (exports) on the device, allocated at the first
+    // the host and (exports) on the device, allocated by the rule beside StageRule
     uint8_t *stage_dev = nullptr, *stage_host = nullptr;
+    bool moved[2] = {false, false};   // a map of some size was exported, imported before
     hipEvent_t stage_ev[2] = {nullptr, nullptr};
 
     // swapping (section "Swapping"), set up by itm_scene_enable_swapping: the
@@ -1040,11 +1041,13 @@ itm_status allocated_blocks(itm_scene *sc, int64_t *n)
     return ITM_OK;
 }
 
-// the n allocated blocks (key and entry) in key order (x, y, z), in the device's reach.
-// Asynchronous.
-itm_status sorted_blocks(itm_scene *sc, int64_t n, CallMem &mem, SortedBlocks *b)
+// the n allocated blocks (key and entry) in key order (x, y, z), in the device's reach,
+// and extra bytes of memory.  Asynchronous.
+itm_status sorted_blocks(itm_scene *sc, int64_t n, CallMem &mem, SortedBlocks *b, size_t extra = 0)
 {
-    if (itm_status st = mem.any(40 * (size_t)n, "export list")) return st;
+    const size_t lists = (40 * (size_t)n + 255) / 256 * 256;
+    if (itm_status st = mem.any(lists + extra, "export lists")) return st;
+    b->extra = (uint8_t *)mem.p + lists;
     b->key = (unsigned long long *)mem.p;
     b->key2 = b->key + n;
     b->ent = (int32_t *)(b->key2 + n);
@@ -1078,6 +1081,7 @@ itm_status collect_blocks(itm_scene *sc, std::vector<BlockRec> &recs)
 // blocks' data to the caller's host memory
 // ---------------------------------------------------------------------------
 constexpr size_t kStageBytes = size_t(16) << 20;   // a slot: 4096 blocks of F and W
+constexpr int kExportChunk = 4096;                 // blocks at a time without the staging
 
 // one array of the caller's: bytes per block, in block order
 struct HostPart {
@@ -1085,17 +1089,49 @@ struct HostPart {
     size_t bytes;
 };
 
-// the two pinned slots, with an event each for the copy that reads or writes it;
-// where the memory cannot be had, copies go to and from the caller's pages directly
-itm_status ensure_slots(itm_scene *sc)
+size_t total_bytes(const HostPart *parts, int n_parts, int64_t n)
 {
+    size_t per = 0;
+    for (int k = 0; k < n_parts; k++) per += parts[k].bytes;
+    return per * (size_t)n;
+}
+
+// From how many bytes on a transfer goes through the staging: where the scene has it
+// (have), where it has moved a map that way before and may go on to (again), and where
+// this may be the only one (alone).  The staging's first use takes 2 to 4 ms more than
+// a later one (its pages are mapped as they are first touched), which a map moved once
+// has to earn back.  Measured with the staging and without, in ms:
+//   export, first of a scene: 2000 blocks 3.9 and 0.8, 8192 3.8 and 2.3, 12288 (48 MiB)
+//     4.3 and 6.1; later: 2000 0.67 and 0.66, 4096 0.8 and 1.3, 32768 4.3 and 14;
+//   import, first: 12288 4.3 and 2.9, 16384 4.7 and 3.0, 24576 (96 MiB) 5.5 and 4.2,
+//     32768 6.3 and 5.2, 65536 9.0 and 9.9; later: 8192 1.26 and 1.20, 12288 1.7 and
+//     1.9, 16384 2.0 and 2.5, 32768 3.7 and 5.1.  From 96 MiB on the first export
+//     after it gains what it costs (24576: 3.3 for 5.9).
+struct StageRule {
+    int way;   // 0 out, 1 in
+    size_t have, again, alone;
+};
+constexpr StageRule kStageOut = {0, size_t(4) << 20, kStageBytes, 3 * kStageBytes};
+constexpr StageRule kStageIn = {1, 3 * kStageBytes, 3 * kStageBytes, 6 * kStageBytes};
+
+// whether a transfer of so many bytes goes through the staging; the two pinned slots,
+// with an event each for the copy that reads or writes them, are there then, and
+// (dev) the device's
+bool take_staging(itm_scene *sc, size_t bytes, const StageRule &rule)
+{
+    const bool dev = rule.way == 0;
+    const size_t least = sc->stage_host ? rule.have : sc->moved[rule.way] ? rule.again : rule.alone;
+    if (bytes >= kStageBytes) sc->moved[rule.way] = true;
+    if (bytes < least) return false;
     for (hipEvent_t &e : sc->stage_ev)
-        if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    if (!sc->stage_host && hipHostMalloc((void **)&sc->stage_host, 2 * kStageBytes) != hipSuccess) {
+        if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) e = nullptr;
+    if (!sc->stage_host && hipHostMalloc((void **)&sc->stage_host, 2 * kStageBytes) != hipSuccess)
         sc->stage_host = nullptr;
-        (void)hipGetLastError();
-    }
-    return ITM_OK;
+    if (dev && !sc->stage_dev && hipMalloc((void **)&sc->stage_dev, 2 * kStageBytes) != hipSuccess)
+        sc->stage_dev = nullptr;
+    if (sc->stage_ev[0] && sc->stage_ev[1] && sc->stage_host && (!dev || sc->stage_dev)) return true;
+    (void)hipGetLastError();   // no room: the runtime copies
+    return false;
 }
 
 // Threads that copy chunks of blocks between the caller's arrays and the pinned
@@ -1200,33 +1236,26 @@ private:
     std::vector<std::thread> pool_;
 };
 
-// n blocks' data to the destinations, in chunks through two slots of staging: while
-// a chunk crosses to the pinned slot, the threads copy the one before to the
-// caller's memory.  fill(off, m, dst) enqueues what writes blocks off .. off + m - 1,
-// the parts back to back, to device memory dst.  The caller's arrays are usually
-// fresh, and first touching their pages is what a single thread spends its time on:
-// 128 MiB take 13 ms by one copy into them, 9.5 ms by one thread from pinned memory,
-// 2.3 ms by eight, the transfer 2.4 ms beside them.
+// n blocks' data to the destinations.  fill(off, m, dst) enqueues what writes blocks
+// off .. off + m - 1, the parts back to back, to device memory dst.
+//
+// Small maps (StageRule): chunk by chunk through the given memory of chunk blocks, by
+// the runtime's copies.
+//
+// In chunks through two slots of staging (staged): while a chunk crosses to the
+// pinned slot, the threads copy the one before to the caller's memory.  The caller's
+// arrays are usually fresh, and first touching their pages is what a single thread
+// spends its time on: 128 MiB take 13 ms by one copy into them, 9.5 ms by one thread
+// from pinned memory, 2.3 ms by eight, the transfer 2.4 ms beside them.
 template <typename Fill>
-itm_status stream_out(itm_scene *sc, int64_t n, const HostPart *parts, int n_parts, Fill fill)
+itm_status stream_out(itm_scene *sc, int64_t n, const HostPart *parts, int n_parts, bool staged, uint8_t *direct,
+                      int64_t chunk, Fill fill)
 {
-    if (itm_status st = ensure_slots(sc)) return st;
-    if (!sc->stage_dev && hipMalloc((void **)&sc->stage_dev, 2 * kStageBytes) != hipSuccess) {
-        sc->stage_dev = nullptr;
-        (void)hipGetLastError();
-    }
-    if (!sc->stage_host || !sc->stage_dev) {   // no room for the staging: chunk by chunk, copied by the runtime
-        size_t per = 0;
-        for (int k = 0; k < n_parts; k++) per += parts[k].bytes;
-        const int64_t chunk = std::min(n, (int64_t)(kStageBytes / per));
-        CallMem mem;
-        if (!sc->stage_dev)
-            if (itm_status st = mem.any(per * (size_t)chunk, "export chunk")) return st;
-        uint8_t *dev = sc->stage_dev ? sc->stage_dev : (uint8_t *)mem.p;
+    if (!staged) {
         for (int64_t off = 0; off < n; off += chunk) {
             const int64_t m = std::min(chunk, n - off);
-            const uint8_t *src = dev;
-            HIP_TRY(fill(off, m, dev));
+            const uint8_t *src = direct;
+            HIP_TRY(fill(off, m, direct));
             for (int k = 0; k < n_parts; k++) {
                 HIP_TRY(hipMemcpyAsync(parts[k].p + parts[k].bytes * (size_t)off, src, parts[k].bytes * (size_t)m,
                                        hipMemcpyDefault, sc->stream));
@@ -1261,16 +1290,12 @@ itm_status stream_out(itm_scene *sc, int64_t n, const HostPart *parts, int n_par
 }
 
 // The way in: n blocks' data from the caller's arrays, part k of block i to dst[k] +
-// i * its bytes.  The threads fill one slot while the other crosses.  Enqueued on
-// return (the slots are still read until the stream gets there).  A runtime copy
-// from pageable memory goes through pinned pages too, but with one thread: an import
-// of 32768 blocks (128 MiB) took 4.91 ms so, now 3.66; of 16384 2.56 and 2.11, of
-// 8192 1.20 and 1.26, so below three slots' worth it is left to the runtime.
-hipError_t stream_in(itm_scene *sc, int64_t n, const HostPart *parts, int n_parts, uint8_t *const *dst)
+// i * its bytes.  Enqueued on return (the slots are still read until the stream gets
+// there).  A runtime copy from pageable memory goes through pinned pages too, but
+// with one thread; staged, the threads fill one slot while the other crosses.
+hipError_t stream_in(itm_scene *sc, int64_t n, const HostPart *parts, int n_parts, bool staged, uint8_t *const *dst)
 {
-    size_t per = 0;
-    for (int k = 0; k < n_parts; k++) per += parts[k].bytes;
-    if (per * (size_t)n < 3 * kStageBytes || ensure_slots(sc) != ITM_OK || !sc->stage_host) {
+    if (!staged) {
         hipError_t e = hipSuccess;
         for (int k = 0; k < n_parts && e == hipSuccess; k++)
             e = hipMemcpyAsync(dst[k], parts[k].p, parts[k].bytes * (size_t)n, hipMemcpyDefault, sc->stream);
@@ -1314,26 +1339,29 @@ itm_status itm_export_blocks(itm_scene *sc, int32_t *coords, float *sdf, float *
     if (!coords && !sdf && !w) return ITM_OK;
     if (capacity < n) return fail(ITM_ERR_ARG, "capacity %lld < %lld blocks", (long long)capacity, (long long)n);
     if (n == 0) return ITM_OK;
+    HostPart parts[2];
+    int n_parts = 0;
+    if (sdf) parts[n_parts++] = HostPart{(uint8_t *)sdf, sizeof(float) * kBlockVox};
+    if (w) parts[n_parts++] = HostPart{(uint8_t *)w, sizeof(float) * kBlockVox};
+    const size_t bytes = sc->swap ? 0 : total_bytes(parts, n_parts, n);
+    const bool staged = bytes && take_staging(sc, bytes, kStageOut);
+    const int64_t chunk = staged || !bytes ? 0 : std::min(n, (int64_t)kExportChunk);
     CallMem mem;
     SortedBlocks b;
-    if (itm_status st = sorted_blocks(sc, n, mem, &b)) return st;
+    if (itm_status st = sorted_blocks(sc, n, mem, &b, total_bytes(parts, n_parts, chunk))) return st;
     if (coords)
         HIP_TRY(hipMemcpyAsync(coords, b.coords, sizeof(int32_t) * 3 * n, hipMemcpyDefault, sc->stream));
     if (!sdf && !w) {
         HIP_TRY(hipStreamSynchronize(sc->stream));
         return ITM_OK;
     }
-    if (!sc->swap) {
-        HostPart parts[2];
-        int k = 0;
-        if (sdf) parts[k++] = HostPart{(uint8_t *)sdf, sizeof(float) * kBlockVox};
-        if (w) parts[k++] = HostPart{(uint8_t *)w, sizeof(float) * kBlockVox};
-        return stream_out(sc, n, parts, k, [&](int64_t off, int64_t m, uint8_t *dst) {
-            float *f = (float *)dst, *wv = sdf ? f + m * kBlockVox : f;
-            return launch_export_floats(sc->fmt, sc->sdf, sc->w, b.out_ent + off, m, sdf ? f : nullptr,
-                                        w ? wv : nullptr, sc->stream);
-        });
-    }
+    if (!sc->swap)
+        return stream_out(sc, n, parts, n_parts, staged, b.extra, chunk,
+                          [&](int64_t off, int64_t m, uint8_t *dst) {
+                              float *f = (float *)dst, *wv = sdf ? f + m * kBlockVox : f;
+                              return launch_export_floats(sc->fmt, sc->sdf, sc->w, b.out_ent + off, m,
+                                                          sdf ? f : nullptr, w ? wv : nullptr, sc->stream);
+                          });
     // with swapping a block's data may sit on the device, on the host, or both
     // (a host copy not merged yet: exported merged, as the swap-in would merge it)
     std::vector<int32_t> ent(n), dblk(sc->n_entries), slots(sc->n_entries);
@@ -1523,11 +1551,12 @@ itm_status itm_import_blocks(itm_scene *sc, const int32_t *coords, const float *
     // a frame of its own: find or insert every key, list it
     FrameGeom g = {};
     FuseArgs a = frame_args(sc, g, false);
+    const bool staged = take_staging(sc, 2 * blk_bytes * (size_t)n, kStageIn);
     auto load = [&](int64_t off, int64_t m) -> hipError_t {
         const HostPart parts[2] = {{(uint8_t *)(sdf + off * kBlockVox), blk_bytes},
                                    {(uint8_t *)(w + off * kBlockVox), blk_bytes}};
         uint8_t *const dst[2] = {(uint8_t *)d_s, (uint8_t *)d_w};
-        return stream_in(sc, m, parts, 2, dst);
+        return stream_in(sc, m, parts, 2, staged, dst);
     };
     hipError_t e = hipSuccess;
     if (n > 0) {
@@ -1582,13 +1611,17 @@ itm_status itm_export_colour(itm_scene *sc, uint8_t *rgbw, int64_t capacity, int
     *n_blocks = n;
     if (!rgbw || n == 0) return ITM_OK;
     if (capacity < n) return fail(ITM_ERR_ARG, "capacity %lld < %lld blocks", (long long)capacity, (long long)n);
+    const HostPart part{rgbw, sizeof(uchar4) * kBlockVox};
+    const size_t bytes = total_bytes(&part, 1, n);
+    const bool staged = take_staging(sc, bytes, kStageOut);
+    const int64_t chunk = staged ? 0 : std::min(n, (int64_t)kExportChunk);
     CallMem mem;
     SortedBlocks b;
-    if (itm_status st = sorted_blocks(sc, n, mem, &b)) return st;
-    const HostPart part{rgbw, sizeof(uchar4) * kBlockVox};
-    return stream_out(sc, n, &part, 1, [&](int64_t off, int64_t m, uint8_t *dst) {
-        return launch_export_colour(sc->clr, b.out_ent + off, m, (uchar4 *)dst, sc->stream);
-    });
+    if (itm_status st = sorted_blocks(sc, n, mem, &b, total_bytes(&part, 1, chunk))) return st;
+    return stream_out(sc, n, &part, 1, staged, b.extra, chunk,
+                      [&](int64_t off, int64_t m, uint8_t *dst) {
+                          return launch_export_colour(sc->clr, b.out_ent + off, m, (uchar4 *)dst, sc->stream);
+                      });
 }
 
 itm_status itm_profile_enable(itm_scene *sc, int enable)

@@ -114,3 +114,26 @@ def test_map_larger_than_the_staging():
         gc, gF, gW = sc.export()
     at = np.lexsort((c[:, 2], c[:, 1], c[:, 0]))
     assert np.array_equal(gc, c[at]) and np.array_equal(gF, F[at]) and np.array_equal(gW, W[at])
+
+
+@pytest.mark.parametrize("n", [3, 1025, 4097, 12287, 24577])
+def test_every_way_out_and_in(n):
+    """A scene's first transfers and its later ones, whole and one array at a time: sizes
+    on either side of those from which the staging is taken (4, 16, 48 and 96 MiB), odd
+    so that the memory behind the lists needs its alignment."""
+    itm, torch = gpu()
+    c, F, W = _map(n, n)
+    at = np.lexsort((c[:, 2], c[:, 1], c[:, 0]))
+    print(f"case: {n} blocks", flush=True)
+    with _scene(itm, n, "f32") as sc:
+        sc.enable_colour()
+        for k in range(3):
+            f = F * np.float32(1 - k / 4)
+            sc.import_blocks(c, f, W)
+            gc, gF, gW = sc.export()
+            assert np.array_equal(gc, c[at]) and np.array_equal(gF, f[at]) and np.array_equal(gW, W[at])
+            out, m = np.full((n, 512), np.nan, np.float32), C.c_int64(0)
+            itm._check(itm.lib().itm_export_blocks(sc.h, None, None, out.ctypes.data, n, C.byref(m)))
+            assert np.array_equal(out, W[at])
+            rgbw = sc.export_colour()
+            assert rgbw.shape == (n, 512, 4) and not rgbw.any()
