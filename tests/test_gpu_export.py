@@ -137,3 +137,33 @@ def test_every_way_out_and_in(n):
             assert np.array_equal(out, W[at])
             rgbw = sc.export_colour()
             assert rgbw.shape == (n, 512, 4) and not rgbw.any()
+
+
+@pytest.mark.parametrize("n", [1, 2, 64, 65])
+def test_small_imports(n):
+    """Up to 64 blocks are checked on the host, more on the device: the same refusals, the
+    first bad voxel named, and nothing changed by them."""
+    itm, torch = gpu()
+    c, F, W = _map(n, 40 + n)
+    at = np.lexsort((c[:, 2], c[:, 1], c[:, 0]))
+    print(f"case: {n} blocks", flush=True)
+    with _scene(itm, n, "f32") as sc:
+        sc.import_blocks(c[:0], F[:0], W[:0])
+        if n > 1:
+            d = c.copy()
+            d[n - 1] = d[0]
+            with pytest.raises(itm.ItmError, match="twice"):
+                sc.import_blocks(d, F, W)
+        last = n * 512 - 1
+        for v, name, x in ((last, "F", np.nan), (0, "F", -1.0001), (last, "W", 2.5), (1, "W", 101.0), (2, "W", -1.0),
+                           (3, "F", -np.inf), (last, "W", np.inf), (4, "W", np.nan)):
+            f, w = F.copy(), W.copy()
+            w[n - 1, 511] = 0.5    # a later one, unless it is the one
+            (f if name == "F" else w).reshape(-1)[v] = x
+            with pytest.raises(itm.ItmError, match=f"voxel {v}: {name}"):
+                sc.import_blocks(c, f, w)
+        assert sc.stats()["n_allocated"] == 0
+        F[0, 0], F[n - 1, 511], W[0, 1], W[n - 1, 510] = -1.0, 1.0, 0.0, 100.0
+        sc.import_blocks(c, F, W)
+        gc, gF, gW = sc.export()
+    assert np.array_equal(gc, c[at]) and np.array_equal(gF, F[at]) and np.array_equal(gW, W[at])
