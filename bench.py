@@ -35,15 +35,15 @@ VOX_BYTES = {"f32": 8, "f16": 4, "s16u8": 3}
 #   --no-cpu-baseline --no-learned --no-colour --no-track --calib-copy-mb 256
 # (summaries under profiles/).  FETCH_SIZE counts 64 B per read request while
 # these kernels' read requests are 128 B (TCC_EA0_RDREQ_128B): the reference
-# elementwise kernel that reads 256 MiB reports 131,087 KiB, hence the factor 2;
+# elementwise kernel that reads 256 MiB reports 131,088 KiB, hence the factor 2;
 # WRITE_SIZE reports the 256 MiB it writes exactly.  `src` is a SHA-256 prefix of
 # the kernel's source files when the counters were taken; a changed kernel, or
 # another frame range, reports traffic null.
-FETCH_SCALE, WRITE_SCALE = 262144.0 / 131087.7, 262144.0 / 262144.0
+FETCH_SCALE, WRITE_SCALE = 262144.0 / 131088.1, 262144.0 / 262144.0
 TRAFFIC_KIB = {
-    ("alloc", "f32", "vga", "10..299"): {"fetch": 1064.7, "write": 1020.6, "src": "7284a72713b31fec"},
-    ("integrate", "f32", "vga", "10..299"): {"fetch": 9988.8, "write": 14773.9, "src": "7284a72713b31fec"},
-    ("raycast", "f32", "vga", "10..299"): {"fetch": 11698.7, "write": 9600.0, "src": "079e19b4e6ef148a"},
+    ("alloc", "f32", "vga", "10..299"): {"fetch": 1064.6, "write": 1020.7, "src": "3e3c43d516254b9c"},
+    ("integrate", "f32", "vga", "10..299"): {"fetch": 10016.6, "write": 14806.7, "src": "3e3c43d516254b9c"},
+    ("raycast", "f32", "vga", "10..299"): {"fetch": 8906.3, "write": 9600.0, "src": "4c8d580f9fcf7009"},
 }
 
 

@@ -139,10 +139,10 @@ __device__ __forceinline__ uint32_t colour_step(uint32_t c, uint32_t s, float ca
     return out;
 }
 
-// Waves per block.  With colour each takes half a block: a whole one needs 92
-// registers and runs 5 waves per SIMD, a half 61 (24.4 and 22.2 us at 640x480 in
-// S16U8).  Without colour the halves only repeat the block's own arithmetic (16.9
-// and 16.7 us at 640x480 in F32, 38.2 and 39.0 at 1280x720 in F16).
+// Waves per block.  With colour each takes half a block: a whole one needs 105 to 112
+// registers (held to 92 for 5 waves per SIMD), a half 73 to 79 and runs 6 (24.4 and
+// 22.2 us at 640x480 in S16U8).  Without colour the halves only repeat the block's own
+// arithmetic (16.9 and 16.7 us at 640x480 in F32, 38.2 and 39.0 at 1280x720 in F16).
 template <bool CLR>
 constexpr int kParts = CLR ? 2 : 1;
 

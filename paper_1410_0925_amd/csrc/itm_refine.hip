@@ -105,9 +105,10 @@ __device__ __forceinline__ void next_weights(int r, const uint16_t *W, bool flip
 //
 // In training (NZ = 4, two waves per SIMD) the reads run a plane ahead of the
 // products: issued as they were used, two at a time, each convolution took twice
-// what its reads take, and a training step 458 us per 8 (now 424).  Inference (NZ =
-// 8, three waves per SIMD) has neither the registers for it (68 spilled) nor the
-// need.  after(r) runs behind the products of plane r.
+// what its reads take, and 8 training steps of 256 blocks 458 us (with this 424, with
+// the weight gradients' reads ahead too 413).  Inference (NZ = 8, three waves per
+// SIMD) has neither the registers for it (68 spilled) nor the need.  after(r) runs
+// behind the products of plane r.
 template <int NZ, typename After>
 __device__ __forceinline__ void conv16(const uint16_t *grid, i32x4 (&w)[14], int yp, int z0, int lane,
                                        f32x4 (&acc)[NZ], After after)
@@ -305,8 +306,9 @@ __global__ __launch_bounds__(kInferThreads) __attribute__((amdgpu_waves_per_eu(3
 // convolutions read, which holds the back-propagated gradient afterwards (142 KB:
 // one workgroup per CU).  A batch of 256 blocks is one block per CU, so the time is
 // one block's chain of layers, bound by its LDS reads (14 us at their rate) and the
-// waits between them: 37.5 us (68 with 16 waves of 2 tiles and activations copied to
-// channel rows layer by layer, 43 with nothing read ahead).
+// waits between them: 37.7 us in a run of steps, 40.3 where other work lies between
+// (in a run of steps 68 with 16 waves of 2 tiles and activations copied to channel rows
+// layer by layer, 43 with nothing read ahead).
 constexpr int kTrainWaves = 8, kTrainNZ = 4;
 constexpr int kRowT = 512 + 8;
 constexpr int kRowA = 100 * 8 + 8;

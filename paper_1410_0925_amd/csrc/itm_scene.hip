@@ -124,7 +124,7 @@ struct itm_scene {
     int32_t *blk = nullptr;           // [n_entries] device block held, -1 none
     uint8_t *onhost = nullptr;        // [n_entries] a host copy exists (not merged yet when blk >= 0)
     int32_t *pool_stack = nullptr;    // [vba_cap] free device blocks
-    int32_t *pool_top = nullptr;      // [2]: stack top, then the scan counts' home (unused)
+    int32_t *pool_top = nullptr;      // stack top
     unsigned long long *pool_noblock = nullptr;
     SwapRec *swap_in_list = nullptr, *swap_out_list = nullptr;   // [n_entries] each
     SwapCnt *swap_cnt = nullptr;      // [2], one per frame parity
@@ -1452,7 +1452,7 @@ itm_status itm_scene_enable_swapping(itm_scene *sc, int64_t device_blocks, int32
     if (dev_alloc((void **)&sc->blk, sizeof(int32_t) * sc->n_entries, "entry blocks") ||
         dev_alloc((void **)&sc->onhost, sc->n_entries, "host flags") ||
         dev_alloc((void **)&sc->pool_stack, sizeof(int32_t) * device_blocks, "block pool") ||
-        dev_alloc((void **)&sc->pool_top, sizeof(int32_t) * 2, "pool top") ||
+        dev_alloc((void **)&sc->pool_top, sizeof(int32_t), "pool top") ||
         dev_alloc((void **)&sc->pool_noblock, sizeof(unsigned long long), "pool misses") ||
         dev_alloc((void **)&sc->swap_in_list, sizeof(SwapRec) * sc->n_entries, "swap-in candidates") ||
         dev_alloc((void **)&sc->swap_out_list, sizeof(SwapRec) * sc->n_entries, "swap-out candidates") ||

@@ -284,7 +284,7 @@ hipError_t launch_swap_choose(const SwapSelArgs &a, bool late, hipStream_t st)
 // full: a copy of 8 + 8 MiB took 210 us with 128 workgroups, 231 with 512, 244 with
 // 4096 (and 155 us in one direction alone), 2048 + 2048 blocks in F32 214 us.
 // With the lists sorted on the host and the blocks copied through a buffer between
-// the device and their slots, a VGA frame with these transfers took 1855 us, now 369.
+// the device and their slots, a VGA frame with these transfers took 2003 us, now 374.
 template <int FMT>
 __global__ __launch_bounds__(256) void k_swap_move(SwapMoveArgs a)
 {
